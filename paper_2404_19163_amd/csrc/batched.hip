@@ -88,8 +88,7 @@ struct BMat {
 // matrix, 4 waves.
 template <int T>
 using X3G = X3Cfg<T, T, 32, 2, 2>;
-using F64_64 = F64Cfg<64, 64, 16, 2, 2>;
-static_assert(F64_64::NT == 256, "the grouped FP64 kernel runs 256-thread blocks");
+using F64_64 = F64Cfg<64>;
 
 __device__ __forceinline__ bool op_applies(int op, const BMat& M) {
   const int phase = M.phase, action = M.action;
@@ -214,7 +213,7 @@ __global__ void __launch_bounds__(256, 4)
     grouped_f64_kernel(const TileTask* __restrict__ tasks, const int* __restrict__ seg,
                        const BMat* __restrict__ mats, int op, double* partials,
                        const int* __restrict__ live) {
-  __shared__ double lds[2 * F64_64::STAGE];
+  __shared__ __attribute__((aligned(16))) double lds[F64_64::LDS];
   __shared__ double red[4];
   if (*live == 0) return;  // no matrix in this stage
   int t0, t1, step;
@@ -250,7 +249,8 @@ __global__ void __launch_bounds__(256, 4)
       const int tiles = np / T;
       pidx = tk.ti * tiles - tk.ti * (tk.ti - 1) / 2 + (tk.tj - tk.ti);
     }
-    f64_tile<64, 64, 16, 2, 2>(a, np, b, np, np, tk.ti * 64, tk.tj * 64, mode, ep, pidx, lds, red);
+    f64_tile<64, 64, F64_64::WM, F64_64::WN, F64_64::NS>(a, np, b, np, np, tk.ti * 64, tk.tj * 64,
+                                                         mode, ep, pidx, lds, red);
     __syncthreads();
   }
 }

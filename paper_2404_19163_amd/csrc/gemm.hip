@@ -74,20 +74,20 @@ __global__ void __launch_bounds__(WM* WN * 64)
 // ---------------------------------------------------------------------------
 // FP64 kernel
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int BK, int WM, int WN, bool SYM>
-__global__ void __launch_bounds__(WM* WN * 64, 2)
+template <int T, bool SYM>
+__global__ void __launch_bounds__(F64Cfg<T>::NT, 4)
     gemm_f64_kernel(const double* __restrict__ A, int lda, const double* __restrict__ B, int ldb,
                     int K, int tiles_n, int gm, EpiParams ep) {
-  using C = F64Cfg<BM, BN, BK, WM, WN>;
-  __shared__ double lds[2 * C::STAGE];
+  using C = F64Cfg<T>;
+  __shared__ __attribute__((aligned(16))) double lds[C::LDS];
   __shared__ double red[C::NT / 64];
   if (ep.gate && *ep.gate) return;
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   int ti, tj;
   tile_coords(bid, tiles_n, SYM, ti, tj, gm);
   const int mode = SYM ? (ti == tj ? 2 : 1) : 0;
-  f64_tile<BM, BN, BK, WM, WN>(A, lda, B, ldb, K, ti * BM, tj * BN, mode, ep,
-                               tile_index(ti, tj, tiles_n, SYM), lds, red);
+  f64_tile<T, T, C::WM, C::WN, C::NS>(A, lda, B, ldb, K, ti * T, tj * T, mode, ep,
+                                      tile_index(ti, tj, tiles_n, SYM), lds, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -124,15 +124,21 @@ int x3_tile_edge(int M, int N, bool sym) {
 int x3_blocks(int M, int N, bool sym) { return grid_blocks(M, N, x3_tile_edge(M, N, sym), sym); }
 
 
-// FP64 tile edge: 64.  The 64-wide tile runs four blocks per CU at the same
-// per-flop rate as the 128-wide one (both ~82% of FP64 peak on full N = 4096
-// grids) and quantizes far better on triangular grids (N = 4096: 2080 blocks
-// instead of 528 on 512 two-per-CU slots).  ZF_F64_TILE / ZF_F64_SYM_TILE = 128
-// select the larger tile (tuning).
+// FP64 tile edge.  A 64-wide tile keeps its CU's matrix cores at 0.9 of their rate, a
+// 32-wide one at 0.7 (twice the operand traffic per flop), but a quarter of the size
+// spreads a small grid over more CUs and ends it in a shorter last round.  So the edge
+// with the lower estimated time of the fullest CU is taken: ceil(tiles / 256) units for 64,
+// 1.3 / 4 of that count's for 32.  Measured, 64- against 32-wide: N = 512 full 19.3 / 7.6 us,
+// N = 1024 full 38.7 / 39.3, symmetric 37.1 / 29.9, N = 2048 full 262 / 331, symmetric
+// 186 / 181, N = 3072 symmetric 519 / 606.  ZF_F64_TILE / ZF_F64_SYM_TILE (32 or 64) force
+// an edge (tuning).
 int f64_tile_edge(int M, int N, bool sym) {
   const char* env = getenv(sym ? "ZF_F64_SYM_TILE" : "ZF_F64_TILE");
-  if (env && atoi(env) == 128 && M % 128 == 0 && N % 128 == 0) return 128;
-  return 64;
+  const int want = env ? atoi(env) : 0;
+  if (want == 32 || want == 64) return want;
+  const int c64 = (grid_blocks(M, N, 64, sym) + 255) / 256;
+  const int c32 = (grid_blocks(M, N, 32, sym) + 255) / 256;
+  return 1.3 * c32 < 4.0 * c64 ? 32 : 64;
 }
 
 // Row-group height of the full-grid tile order: 4 (a run of 32 tiles on one XCD then
@@ -155,7 +161,7 @@ static int sym_group() {
 
 int f64_blocks(int M, int N, bool sym) { return grid_blocks(M, N, f64_tile_edge(M, N, sym), sym); }
 
-int max_blocks(int M, int N) { return grid_blocks(M, N, 64, false); }
+int max_blocks(int M, int N) { return grid_blocks(M, N, 32, false); }
 
 template <int BM, int BN, int WM, int WN, int PM, int NS = 2>
 static void x3_launch(const u16* Ahi, const u16* Alo, int lda, const u16* Bhi, const u16* Blo,
@@ -182,16 +188,15 @@ static void f32_launch(const float* A, int lda, const float* B, int ldb, int M, 
                        0, st, A, lda, B, ldb, K, N / BN, tile_group(M, BM), ep);
 }
 
-template <int BM, int BN, int WM, int WN>
+template <int T>
 static void f64_launch(const double* A, int lda, const double* B, int ldb, int M, int N, int K,
                        bool sym, int blocks, const EpiParams& ep, hipStream_t st) {
   if (sym)
-    hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, 16, WM, WN, true>), dim3(blocks),
-                       dim3(WM * WN * 64), 0, st, A, lda, B, ldb, K, N / BN, sym_group(), ep);
+    hipLaunchKernelGGL((gemm_f64_kernel<T, true>), dim3(blocks), dim3(F64Cfg<T>::NT), 0, st, A,
+                       lda, B, ldb, K, N / T, sym_group(), ep);
   else
-    hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, 16, WM, WN, false>), dim3(blocks),
-                       dim3(WM * WN * 64), 0, st, A, lda, B, ldb, K, N / BN, tile_group(M, BM),
-                       ep);
+    hipLaunchKernelGGL((gemm_f64_kernel<T, false>), dim3(blocks), dim3(F64Cfg<T>::NT), 0, st, A,
+                       lda, B, ldb, K, N / T, tile_group(M, T), ep);
 }
 
 template <int PM>
@@ -258,10 +263,10 @@ hipError_t launch_gemm_f64(const double* A, int lda, const double* B, int ldb, i
                            bool sym, const EpiParams& ep, hipStream_t st) {
   if (!dims_ok(M, N, K, sym)) return hipErrorInvalidValue;
   const int blocks = f64_blocks(M, N, sym);
-  if (f64_tile_edge(M, N, sym) == 128)
-    f64_launch<128, 128, 2, 2>(A, lda, B, ldb, M, N, K, sym, blocks, ep, st);
+  if (f64_tile_edge(M, N, sym) == 32)
+    f64_launch<32>(A, lda, B, ldb, M, N, K, sym, blocks, ep, st);
   else
-    f64_launch<64, 64, 2, 2>(A, lda, B, ldb, M, N, K, sym, blocks, ep, st);
+    f64_launch<64>(A, lda, B, ldb, M, N, K, sym, blocks, ep, st);
   return hipGetLastError();
 }
 

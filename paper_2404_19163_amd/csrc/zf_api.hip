@@ -1166,7 +1166,7 @@ int zf_residual(const double* S, const double* Z, int n, double* rms, void* stre
 constexpr int kNoAllocMaxN = 1024;
 constexpr int kNoAllocNp = 1024;  // pad_order(kNoAllocMaxN)
 constexpr size_t kNoAllocMat = (size_t)kNoAllocNp * kNoAllocNp;
-constexpr int kNoAllocParts = (kNoAllocNp / 64) * (kNoAllocNp / 64);  // max_blocks(np, np)
+constexpr int kNoAllocParts = (kNoAllocNp / 32) * (kNoAllocNp / 32);  // max_blocks(np, np)
 static __device__ __align__(256) double scratch[3 * kNoAllocMat + kNoAllocParts];
 
 // Device address of `scratch` on each device, looked up once per device with that

@@ -21,18 +21,14 @@ struct X3Cfg {
   static_assert(BM % (WM * 32) == 0 && BN % (WN * 32) == 0, "wave tile");
 };
 
-template <int BM, int BN, int BK, int WM, int WN>
+// FP64 tile of edge T (64 or 32): 4 waves, each a quarter of the tile.  The 64-wide tile
+// runs four blocks per CU on a two-stage ring, the 32-wide one, for small grids, hides the
+// load latency behind a four-stage ring.
+template <int T>
 struct F64Cfg {
-  static constexpr int NT = WM * WN * 64;
-  static constexpr int WTM = BM / WM, WTN = BN / WN;
-  static constexpr int FM = WTM / 16, FN = WTN / 16;
-  static constexpr int LS = BK + 1;   // LDS row stride in doubles (odd: conflict-free columns)
-  static constexpr int VPR = BK / 2;  // 16-byte vectors per tile row
-  static constexpr int A_PT = BM * VPR / NT, B_PT = BN * VPR / NT;
-  static constexpr int STAGE = (BM + BN) * LS;
-  static_assert(BM % (WM * 16) == 0 && BN % (WN * 16) == 0, "wave tile");
-  static_assert(BK % 4 == 0, "k step");
-  static_assert((BM * VPR) % NT == 0 && (BN * VPR) % NT == 0, "load split");
+  static constexpr int WM = 2, WN = 2, NT = 256;
+  static constexpr int NS = T == 32 ? 4 : 2;
+  static constexpr int LDS = NS * 2 * T * 16;  // doubles
 };
 
 }  // namespace zf
