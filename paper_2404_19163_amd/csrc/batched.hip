@@ -124,7 +124,7 @@ __global__ void __launch_bounds__(X3G<T>::NT, 2)
                       const BMat* __restrict__ mats, int op, double c1, double c2,
                       double* partials, const int* __restrict__ live) {
   using CF = X3G<T>;
-  __shared__ __attribute__((aligned(16))) u16 lds[2 * CF::STAGE_ELEMS];
+  __shared__ __attribute__((aligned(16))) u16 lds[x3_lds(T, T, PM_X3, 2)];
   __shared__ double red[CF::NT / 64];
   if (live && *live == 0) return;  // no matrix in this stage
   int t0, t1, step;
@@ -201,8 +201,8 @@ __global__ void __launch_bounds__(X3G<T>::NT, 2)
       const int tiles = np / T;
       pidx = tk.ti * tiles - tk.ti * (tk.ti - 1) / 2 + (tk.tj - tk.ti);
     }
-    x3_tile<T, T, 32, 2, 2>(ah, al, 32, bh, bl, 32, np, tk.ti * T, tk.tj * T, mode, ep, pidx, lds,
-                            red, 32 * np, 32 * np);
+    x3_tile<T, T, 2, 2, PM_X3, 2>(ah, al, 32, bh, bl, 32, np, tk.ti * T, tk.tj * T, mode, ep, pidx,
+                                  lds, red, 32 * np, 32 * np);
     __syncthreads();
   }
 }

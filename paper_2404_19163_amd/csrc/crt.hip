@@ -151,7 +151,7 @@ __global__ void __launch_bounds__(256) crt_residue_kernel(const double* __restri
 // one int8 product per modulus, reduced to its residue
 // ---------------------------------------------------------------------------
 // 256 x 256 output tiles, 8 waves of 128 x 64, the BF16 tiles' direct-to-LDS
-// mainloop in its int8 mode with a 3-stage ring.  One block per (tile, modulus): the products of the L
+// mainloop in its int8 mode with a 4-stage ring.  One block per (tile, modulus): the products of the L
 // moduli are independent, so a grid of L times the tile count fills the chip even
 // when the tiles alone would not (the symmetric N = 4096 product: 136 tiles, 1904
 // blocks).  The block's int32 sums are reduced to rho_l in [0, m_l) and stored as bytes
@@ -165,10 +165,10 @@ __global__ void __launch_bounds__(512)
                     unsigned char* __restrict__ rho, size_t plane, int np,
                     const int* __restrict__ gate) {
   if (gate && *gate) return;
-  constexpr int BM = 256, BN = 256, WM = 2, WN = 4, NS = 3;
+  constexpr int BM = 256, BN = 256, WM = 2, WN = 4, NS = 4;
   using C = X3Cfg<BM, BN, 32, WM, WN>;
-  // single-product stages of (BM + BN) 32 elements: a 3-stage ring, two stages loading
-  __shared__ __attribute__((aligned(16))) u16 lds[NS * (BM + BN) * 32];
+  // single-product stages of (BM + BN) 32 elements: a 4-stage ring, three stages loading
+  __shared__ __attribute__((aligned(16))) u16 lds[NS * x3_stage(BM, BN, PM_I8)];
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   const int ntiles = gridDim.x / cc.L;
   const int l = bid / ntiles;
@@ -183,9 +183,9 @@ __global__ void __launch_bounds__(512)
     for (int a = 0; a < C::FM; ++a)
 #pragma unroll
       for (int b = 0; b < C::FN; ++b) acc[a][b] = f32x16{};
-    x3_mainloop<BM, BN, 32, WM, WN, PM_I8, NS>(A + (size_t)l * plane16, nullptr, ld16,
-                                           B + (size_t)l * plane16, nullptr, ld16, 0, K16, m0,
-                                           n0, lds, acc);
+    x3_mainloop<BM, BN, WM, WN, PM_I8, NS>(A + (size_t)l * plane16, nullptr, ld16,
+                                           B + (size_t)l * plane16, nullptr, ld16, K16, m0, n0, lds,
+                                           acc, 32, 32);
     const int md = cc.mod[l];
     const float inv = 1.0f / (float)md;
     // a lane holds rows 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32 of each

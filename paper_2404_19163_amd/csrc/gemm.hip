@@ -31,20 +31,19 @@
 namespace zf {
 // SYM is a template parameter so that the two modes are distinct kernels (and show
 // up separately in a kernel trace).
-template <int BM, int BN, int BK, int WM, int WN, bool SYM, int PM, int NS>
-__global__ void __launch_bounds__(WM* WN * 64)
+template <int BM, int BN, int WM, int WN, bool SYM, int PM, int NS, int OCC>
+__global__ void __launch_bounds__(WM* WN * 64, OCC)
     gemm_x3_kernel(const u16* __restrict__ Ahi, const u16* __restrict__ Alo, int lda,
                    const u16* __restrict__ Bhi, const u16* __restrict__ Blo, int ldb, int K,
                    int tiles_n, int gm, EpiParams ep, int ksa, int ksb) {
-  using C = X3Cfg<BM, BN, BK, WM, WN>;
-  __shared__ __attribute__((aligned(16))) u16 lds[NS * C::STAGE_ELEMS];
-  __shared__ double red[C::NT / 64];
+  __shared__ __attribute__((aligned(16))) u16 lds[x3_lds(BM, BN, PM, NS)];
+  __shared__ double red[WM * WN];
   if (ep.gate && *ep.gate) return;
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   int ti, tj;
   tile_coords(bid, tiles_n, SYM, ti, tj, gm);
   const int mode = SYM ? (ti == tj ? 2 : 1) : 0;
-  x3_tile<BM, BN, BK, WM, WN, PM, NS>(Ahi, Alo, lda, Bhi, Blo, ldb, K, ti * BM, tj * BN, mode, ep,
+  x3_tile<BM, BN, WM, WN, PM, NS>(Ahi, Alo, lda, Bhi, Blo, ldb, K, ti * BM, tj * BN, mode, ep,
                                   tile_index(ti, tj, tiles_n, SYM), lds, red, ksa, ksb);
 }
 
@@ -103,21 +102,33 @@ static int grid_blocks(int M, int N, int t, bool sym) {
   return sym ? tm * (tm + 1) / 2 : tm * tn;
 }
 
-// Tile edge of a launch: 256 when it divides both output dimensions and yields at
-// least 128 workgroups (half of the 256 CUs: fewer, larger tiles beat more, smaller
-// ones down to that point), else 128 when that yields at least 192 workgroups (the
-// 128-wide tile runs one 8-wave block per CU), else 64.  Measured on the mixed solve:
-// 64-wide tiles beat 128-wide grids of 136-171 tiles (N = 1536, 2048, 2304) by 3-6%,
-// 128-wide ones win from about 200 tiles on (N = 2560, 2816).  ZF_X3_TILE /
-// ZF_X3_SYM_TILE (64, 128 or 256) force the BF16x3 edge when it divides (tuning).
+// Tile edge of a launch.  Per flop the 256-wide tile is the fastest and the 64-wide the
+// slowest (operand traffic), but each needs a grid that fills the 256 CUs, where a 256- or
+// 128-wide block takes a CU for itself:
+//  - 256 from 160 tiles on, from 128 on in symmetric mode.  Full N = 3584 (196 tiles) 237 us
+//    against 275 with 128-wide tiles, N = 3072 (144) 195 / 181.  Symmetric N = 5120 (210)
+//    353 / 435; at N = 4096 (136) one launch takes 261 / 250, but under sustained load, when
+//    the clock follows the energy used, the mixed solve takes 11.0 ms against 11.2.
+//  - else 128 from 192 tiles on.  Full N = 1792 (196) 43 us against 48 with 64-wide tiles,
+//    N = 1536 (144) 37 / 35; symmetric N = 2560 (210) 66 / 76, N = 2304 (171) 59 / 58.
+//  - but not where 128-wide tiles would leave a second round mostly empty while 64-wide
+//    ones fill the chip evenly: symmetric N = 3072 (300 tiles) 135 us against 118, N = 3584
+//    (406) 162 / 214.
+//  - else 64.
+// (Overlap matrices, means over a mixed solve.)  ZF_X3_TILE / ZF_X3_SYM_TILE (64, 128 or
+// 256) force the edge when it divides (tuning).
 int x3_tile_edge(int M, int N, bool sym) {
   const char* env = getenv(sym ? "ZF_X3_SYM_TILE" : "ZF_X3_TILE");
   if (env) {
     const int want = atoi(env);
     if ((want == 64 || want == 128 || want == 256) && M % want == 0 && N % want == 0) return want;
   }
-  if (M % 256 == 0 && N % 256 == 0 && grid_blocks(M, N, 256, sym) >= 128) return 256;
-  if (M % 128 == 0 && N % 128 == 0 && grid_blocks(M, N, 128, sym) >= 192) return 128;
+  if (M % 256 == 0 && N % 256 == 0 && grid_blocks(M, N, 256, sym) >= (sym ? 128 : 160))
+    return 256;
+  if (M % 128 == 0 && N % 128 == 0) {
+    const int t = grid_blocks(M, N, 128, sym);
+    if (t >= 192 && !(sym && t > 256 && t <= 352)) return 128;
+  }
   return 64;
 }
 
@@ -128,7 +139,7 @@ int x3_blocks(int M, int N, bool sym) { return grid_blocks(M, N, x3_tile_edge(M,
 // 32-wide one at 0.7 (twice the operand traffic per flop), but a quarter of the size
 // spreads a small grid over more CUs and ends it in a shorter last round.  So the edge
 // with the lower estimated time of the fullest CU is taken: ceil(tiles / 256) units for 64,
-// 1.3 / 4 of that count's for 32.  Measured, 64- against 32-wide: N = 512 full 19.3 / 7.6 us,
+// 1.2 / 4 of that count's for 32.  Measured, 64- against 32-wide: N = 512 full 19.3 / 7.6 us,
 // N = 1024 full 38.7 / 39.3, symmetric 37.1 / 29.9, N = 2048 full 262 / 331, symmetric
 // 186 / 181, N = 3072 symmetric 519 / 606.  ZF_F64_TILE / ZF_F64_SYM_TILE (32 or 64) force
 // an edge (tuning).
@@ -138,7 +149,7 @@ int f64_tile_edge(int M, int N, bool sym) {
   if (want == 32 || want == 64) return want;
   const int c64 = (grid_blocks(M, N, 64, sym) + 255) / 256;
   const int c32 = (grid_blocks(M, N, 32, sym) + 255) / 256;
-  return 1.3 * c32 < 4.0 * c64 ? 32 : 64;
+  return 1.2 * c32 < 4.0 * c64 ? 32 : 64;
 }
 
 // Row-group height of the full-grid tile order: 4 (a run of 32 tiles on one XCD then
@@ -163,16 +174,16 @@ int f64_blocks(int M, int N, bool sym) { return grid_blocks(M, N, f64_tile_edge(
 
 int max_blocks(int M, int N) { return grid_blocks(M, N, 32, false); }
 
-template <int BM, int BN, int WM, int WN, int PM, int NS = 2>
+template <int BM, int BN, int WM, int WN, int PM, int NS, int OCC>
 static void x3_launch(const u16* Ahi, const u16* Alo, int lda, const u16* Bhi, const u16* Blo,
                       int ldb, int M, int N, int K, bool sym, int blocks, const EpiParams& ep,
                       hipStream_t st, int ksa, int ksb) {
   if (sym)
-    hipLaunchKernelGGL((gemm_x3_kernel<BM, BN, 32, WM, WN, true, PM, NS>), dim3(blocks),
+    hipLaunchKernelGGL((gemm_x3_kernel<BM, BN, WM, WN, true, PM, NS, OCC>), dim3(blocks),
                        dim3(WM * WN * 64), 0, st, Ahi, Alo, lda, Bhi, Blo, ldb, K, N / BN, sym_group(), ep,
                        ksa, ksb);
   else
-    hipLaunchKernelGGL((gemm_x3_kernel<BM, BN, 32, WM, WN, false, PM, NS>), dim3(blocks),
+    hipLaunchKernelGGL((gemm_x3_kernel<BM, BN, WM, WN, false, PM, NS, OCC>), dim3(blocks),
                        dim3(WM * WN * 64), 0, st, Ahi, Alo, lda, Bhi, Blo, ldb, K, N / BN,
                        tile_group(M, BM), ep, ksa, ksb);
 }
@@ -204,14 +215,17 @@ static void x3_dispatch(const u16* Ahi, const u16* Alo, int lda, const u16* Bhi,
                         int ldb, int M, int N, int K, bool sym, int tile, int blocks,
                         const EpiParams& ep, hipStream_t st, int ksa, int ksb) {
   if (tile == 256)
-    x3_launch<256, 256, 2, 4, PM>(Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, sym, blocks, ep, st, ksa,
-                                  ksb);
-  else if (tile == 128)  // 8 waves of 32 x 64 and a 3-stage ring (loads two stages ahead)
-    x3_launch<128, 128, 4, 2, PM, 3>(Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, sym, blocks, ep, st,
-                                     ksa, ksb);
+    x3_launch<256, 256, 2, 4, PM, 2, 1>(Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, sym, blocks, ep, st,
+                                        ksa, ksb);
+  else if (tile == 128)  // 8 waves of 32 x 64, one block per CU, loads three stages ahead
+    x3_launch<128, 128, 4, 2, PM, 4, 1>(Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, sym, blocks, ep, st,
+                                        ksa, ksb);
+  else if (blocks > 512 && blocks <= 1024)  // one round at four blocks per CU
+    x3_launch<64, 64, 2, 2, PM, 2, 4>(Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, sym, blocks, ep, st,
+                                      ksa, ksb);
   else
-    x3_launch<64, 64, 2, 2, PM>(Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, sym, blocks, ep, st, ksa,
-                                ksb);
+    x3_launch<64, 64, 2, 2, PM, 4, 2>(Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, sym, blocks, ep, st,
+                                      ksa, ksb);
 }
 
 hipError_t launch_gemm_x3(const u16* Ahi, const u16* Alo, int lda, const u16* Bhi, const u16* Blo,

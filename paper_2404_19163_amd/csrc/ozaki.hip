@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(WM* WN * 64, 2)
                    const u16* __restrict__ B, const int* __restrict__ eb, int ld16,
                    size_t plane16, int K16, int s, int tiles_n, int gm, EpiParams ep) {
   using C = X3Cfg<BM, BN, 32, WM, WN>;
-  __shared__ __attribute__((aligned(16))) u16 lds[2 * C::STAGE_ELEMS];
+  __shared__ __attribute__((aligned(16))) u16 lds[2 * x3_stage(BM, BN, PM_I8)];
   __shared__ double red[C::NT / 64];
   if (ep.gate && *ep.gate) return;
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
@@ -124,9 +124,9 @@ __global__ void __launch_bounds__(WM* WN * 64, 2)
       for (int b = 0; b < C::FN; ++b) acc[a][b] = f32x16{};
     for (int p = 1; p < d; ++p) {
       const int q = d - p;
-      x3_mainloop<BM, BN, 32, WM, WN, PM_I8>(A + (size_t)(p - 1) * plane16, nullptr, ld16,
-                                             B + (size_t)(q - 1) * plane16, nullptr, ld16, 0, K16,
-                                             m0, n0, lds, acc);
+      x3_mainloop<BM, BN, WM, WN, PM_I8, 2>(A + (size_t)(p - 1) * plane16, nullptr, ld16,
+                                            B + (size_t)(q - 1) * plane16, nullptr, ld16, K16, m0,
+                                            n0, lds, acc, 32, 32);
     }
     const double w = ldexp(1.0, -7 * d);
 #pragma unroll

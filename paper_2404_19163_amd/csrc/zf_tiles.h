@@ -7,6 +7,17 @@
 
 namespace zf {
 
+// 16-bit elements of one 32-wide K stage of a BM x BN tile: both halves of both operands,
+// or one half (or one plane of bytes) for the single-product modes.
+constexpr int x3_stage(int bm, int bn, int pm) {
+  return ((pm & PM_HH) != 0 || pm == PM_I8 ? 1 : 2) * (bm + bn) * 32;
+}
+// Shared memory of a tile with an NS-stage ring, in 16-bit elements: the ring, which later
+// holds the epilogue's 32-row strips (FP32 accumulators, then FP64 values).
+constexpr int x3_lds(int bm, int bn, int pm, int ns) {
+  return ns * x3_stage(bm, bn, pm) > 192 * (bn + 1) ? ns * x3_stage(bm, bn, pm) : 192 * (bn + 1);
+}
+
 template <int BM, int BN, int BK, int WM, int WN>
 struct X3Cfg {
   static constexpr int NT = WM * WN * 64;
