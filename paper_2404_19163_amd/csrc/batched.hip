@@ -124,7 +124,7 @@ __global__ void __launch_bounds__(X3G<T>::NT, 2)
                       const BMat* __restrict__ mats, int op, double c1, double c2,
                       double* partials, const int* __restrict__ live) {
   using CF = X3G<T>;
-  __shared__ __attribute__((aligned(16))) u16 lds[x3_lds(T, T, PM_X3, 2)];
+  __shared__ __attribute__((aligned(16))) u16 lds[x3_lds(T, T, PM_X3, 2, 4)];
   __shared__ double red[CF::NT / 64];
   if (live && *live == 0) return;  // no matrix in this stage
   int t0, t1, step;

@@ -36,7 +36,7 @@ __global__ void __launch_bounds__(WM* WN * 64, OCC)
     gemm_x3_kernel(const u16* __restrict__ Ahi, const u16* __restrict__ Alo, int lda,
                    const u16* __restrict__ Bhi, const u16* __restrict__ Blo, int ldb, int K,
                    int tiles_n, int gm, EpiParams ep, int ksa, int ksb) {
-  __shared__ __attribute__((aligned(16))) u16 lds[x3_lds(BM, BN, PM, NS)];
+  __shared__ __attribute__((aligned(16))) u16 lds[x3_lds(BM, BN, PM, NS, WM * WN)];
   __shared__ double red[WM * WN];
   if (ep.gate && *ep.gate) return;
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
@@ -53,7 +53,8 @@ __global__ void __launch_bounds__(WM* WN * 64)
     gemm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb,
                     int K, int tiles_n, int gm, EpiParams ep) {
   using C = X3Cfg<BM, BN, 32, WM, WN>;
-  __shared__ __attribute__((aligned(16))) u16 lds[2 * C::STAGE_ELEMS];
+  // two stages of 16 floats per row: as many bytes as a single-product 16-bit stage
+  __shared__ __attribute__((aligned(16))) u16 lds[x3_lds(BM, BN, PM_HH, 2, WM * WN)];
   __shared__ double red[C::NT / 64];
   if (ep.gate && *ep.gate) return;
   const int bid = xcd_remap(blockIdx.x, gridDim.x);

@@ -12,10 +12,12 @@ namespace zf {
 constexpr int x3_stage(int bm, int bn, int pm) {
   return ((pm & PM_HH) != 0 || pm == PM_I8 ? 1 : 2) * (bm + bn) * 32;
 }
-// Shared memory of a tile with an NS-stage ring, in 16-bit elements: the ring, which later
-// holds the epilogue's 32-row strips (FP32 accumulators, then FP64 values).
-constexpr int x3_lds(int bm, int bn, int pm, int ns) {
-  return ns * x3_stage(bm, bn, pm) > 192 * (bn + 1) ? ns * x3_stage(bm, bn, pm) : 192 * (bn + 1);
+// Shared memory the epilogue takes per wave, in 16-bit elements: a 32 x 33 block of doubles.
+constexpr int kEpiWave = 32 * 33 * 4;
+// Shared memory of a tile with an NS-stage ring and nw waves, in 16-bit elements: the ring,
+// whose place the epilogue takes after the main loop.
+constexpr int x3_lds(int bm, int bn, int pm, int ns, int nw) {
+  return ns * x3_stage(bm, bn, pm) > nw * kEpiWave ? ns * x3_stage(bm, bn, pm) : nw * kEpiWave;
 }
 
 template <int BM, int BN, int BK, int WM, int WN>
@@ -23,11 +25,6 @@ struct X3Cfg {
   static constexpr int NT = WM * WN * 64;
   static constexpr int WTM = BM / WM, WTN = BN / WN;
   static constexpr int FM = WTM / 32, FN = WTN / 32;
-  static constexpr int STAGE = (BM + BN) * 2 * BK;  // 16-bit elements per pipeline stage
-  static constexpr int SP = BN + 1;                  // epilogue strip pitch (elements)
-  // the two stage buffers also hold the epilogue's 32-row strips: FP32 accumulators
-  // then FP64 values, 32 SP (4 + 8) bytes = 192 SP 16-bit elements
-  static constexpr int STAGE_ELEMS = (2 * STAGE > 192 * SP) ? STAGE : 96 * SP;
   static_assert(BK == 32, "the LDS swizzle assumes 64-byte tile rows");
   static_assert(BM % (WM * 32) == 0 && BN % (WN * 32) == 0, "wave tile");
 };

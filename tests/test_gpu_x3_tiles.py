@@ -36,3 +36,27 @@ def test_edges_agree_bitwise(zf, monkeypatch, prec, n, sym):
     for tile in ("128", "256"):
         assert torch.equal(out[tile][0], out["64"][0])
         assert out[tile][1] == pytest.approx(out["64"][1], rel=1e-12)
+
+
+@pytest.mark.parametrize("tile", ["64", "128", "256"])
+@pytest.mark.parametrize("n", [1, 31, 33, 65, 260])
+def test_symmetric_epilogue(zf, monkeypatch, tile, n):
+    """alpha D + beta A A^T + gamma I around the diagonal blocks: exactly symmetric, within
+    the split product's bound 3 K u32 (|A_h| + |A_l|)(|A_h| + |A_l|)^T plus its 3 u^2 |A||A|^T
+    (u = 2^-8), and a norm that counts every element once."""
+    monkeypatch.setenv("ZF_X3_SYM_TILE", tile)
+    rng = np.random.default_rng(n)
+    k = 48
+    A = rng.standard_normal((n, k))
+    D = rng.standard_normal((n, n))
+    D = D + D.T
+    al, be, ga = 0.75, -1.25, 2.0
+    C, s = zf.t_gemm("bf16x3", torch.from_numpy(A).cuda(), torch.from_numpy(A).cuda(), sym=True,
+                     alpha=al, D=torch.from_numpy(D).cuda(), beta=be, gamma=ga, kblocked=True)
+    C = C.cpu().numpy()
+    assert np.array_equal(C, C.T)
+    ref = al * D + be * (A @ A.T) + ga * np.eye(n)
+    absx = np.abs(A) @ np.abs(A).T
+    bound = abs(be) * (3 * 2.0 ** -16 + 3 * k * 2.0 ** -24 * 1.02) * absx * 1.01 + 1e-14
+    assert np.all(np.abs(C - ref) <= bound)
+    assert s == pytest.approx(np.sum(C * C), rel=1e-12)
