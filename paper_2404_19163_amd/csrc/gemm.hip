@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(WM* WN * 64)
 #pragma unroll
     for (int b = 0; b < C::FN; ++b) acc[a][b] = f32x16{};
   f32_mainloop<BM, BN, WM, WN>(A, lda, B, ldb, 0, K, ti * BM, tj * BN, lds, acc);
-  x3_epilogue<BM, BN, 32, WM, WN>(acc, ti * BM, tj * BN, mode, ep, tile_index(ti, tj, tiles_n, SYM),
+  x3_epilogue<BM, BN, 32, WM, WN, PAIR_BF16>(acc, ti * BM, tj * BN, mode, ep, tile_index(ti, tj, tiles_n, SYM),
                                   lds, red);
 }
 

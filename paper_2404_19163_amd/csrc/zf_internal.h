@@ -23,13 +23,16 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------------------
-// FP32 -> BF16 with round to nearest, ties to even (NaN kept quiet).
+// FP32 -> BF16 with round to nearest, ties to even, by the hardware convert.  The empty
+// statement hides where the value comes from: given an FP64 value rounded to FP32, the
+// compiler would convert it to BF16 in one rounding, which differs on ties.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ float rounded_f32(float f) {
+  asm("" : "+v"(f));
+  return f;
+}
 __device__ __forceinline__ u16 f32_to_bf16_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (u16)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (u16)(u >> 16);
+  return __builtin_bit_cast(u16, (__bf16)rounded_f32(f));
 }
 __device__ __forceinline__ float bf16_to_f32(u16 h) { return __uint_as_float(((uint32_t)h) << 16); }
 
@@ -56,6 +59,31 @@ __device__ __forceinline__ void split_f16(float x, u16& hi, u16& lo) {
 __device__ __forceinline__ void split_pair(float x, u16& hi, u16& lo, int fmt) {
   if (fmt == PAIR_F16) split_f16(x, hi, lo);
   else split_bf16(x, hi, lo);
+}
+// split_pair of 4 values, packed two to a word: for BF16 three conversions a pair (both
+// halves of a word at once) instead of rounding in integer arithmetic, which took most of
+// the epilogue's instructions.
+typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void split_pair4(const float x[4], u32x2_t& hi, u32x2_t& lo, int fmt) {
+  if (fmt == PAIR_F16) {
+    u16 h[4], l[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) split_f16(x[k], h[k], l[k]);
+    hi = u32x2_t{h[0] | ((unsigned)h[1] << 16), h[2] | ((unsigned)h[3] << 16)};
+    lo = u32x2_t{l[0] | ((unsigned)l[1] << 16), l[2] | ((unsigned)l[3] << 16)};
+    return;
+  }
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {
+    const float x0 = rounded_f32(x[2 * w]), x1 = rounded_f32(x[2 * w + 1]);
+    const unsigned h =
+        __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{x0, x1}), bf16x2));
+    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
+    hi[w] = h;
+    lo[w] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{r0, r1}), bf16x2));
+  }
 }
 __device__ __forceinline__ float pair_sum(u16 hi, u16 lo, int fmt) {
   return fmt == PAIR_F16 ? f16_to_f32(hi) + f16_to_f32(lo) : bf16_to_f32(hi) + bf16_to_f32(lo);
