@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 PKG = os.path.dirname(HERE)
 ROOT = os.path.dirname(PKG)
 BUILD = os.path.join(ROOT, "_build")
-SOURCES = ["gemm.hip", "elementwise.hip", "zf_api.hip", "batched.hip", "guess.hip", "ozaki.hip",
+SOURCES = ["gemm.hip", "elementwise.hip", "zf_api.hip", "batched.hip", "team.hip", "guess.hip", "ozaki.hip",
            "crt.hip"]
 OUT = os.path.join(PKG, "libzf.so")
 

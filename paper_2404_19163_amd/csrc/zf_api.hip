@@ -31,6 +31,7 @@
 #include "zf.h"
 #include "zf_index.h"
 #include "zf_internal.h"
+#include "zf_team.h"
 
 namespace zf {
 
@@ -167,6 +168,12 @@ static void prof_harvest() {
 // ---------------------------------------------------------------------------
 // workspace
 // ---------------------------------------------------------------------------
+constexpr int kTeamHist = 512;  // residuals the one-kernel path can report
+struct TeamReport {
+  TeamOut out;
+  double hist[kTeamHist];
+};
+
 struct Workspace {
   int device = -1;
   int np = 0;
@@ -208,6 +215,10 @@ struct Workspace {
   int* gate = nullptr;
   double* prev_dev = nullptr;
   double *box = nullptr, *box_dev = nullptr;
+  // one-kernel refinement of small orders (team.hip): its meeting point, and its report
+  // and residual history in pinned memory
+  TeamCtl* team_ctl = nullptr;
+  TeamReport *team = nullptr, *team_dev = nullptr;
 };
 constexpr int kBoxSlots = 8;
 
@@ -218,6 +229,7 @@ static void ws_free(Workspace& w) {
   w.allocs.clear();
   if (w.host_err) hipHostFree(w.host_err);
   if (w.box) hipHostFree(w.box);
+  if (w.team) hipHostFree(w.team);
   int dev = w.device;
   w = Workspace();
   w.device = dev;
@@ -272,6 +284,14 @@ static int ws_build(Workspace& w, int dev, int np, bool x3, bool f64, bool f32, 
       hipHostGetDevicePointer((void**)&w.box_dev, w.box, 0) != hipSuccess) {
     (void)hipGetLastError();
     return fail(ZF_ERR_NOMEM, "hipHostMalloc of the stop-test mailbox failed");
+  }
+  ZF_TRY(ws_alloc(w, &w.team_ctl, 1));
+  if (hipMemset(w.team_ctl, 0, sizeof(TeamCtl)) != hipSuccess ||
+      hipHostMalloc((void**)&w.team, sizeof(TeamReport),
+                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+      hipHostGetDevicePointer((void**)&w.team_dev, w.team, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(ZF_ERR_NOMEM, "hipHostMalloc of the report failed");
   }
   // the BF16 pairs of delta and Q and the row-major Z pair serve both phases
   ZF_TRY(ws_alloc(w, &w.d_hi, m));
@@ -899,6 +919,117 @@ static int crt_moduli_env() {
   return (v >= 8 && v <= kCrtMaxModuli) ? v : 14;
 }
 
+// History and result record of a solve that ended with rc (>= 0: an iterate was returned);
+// the call's return code.  two: the second phase's outcome is the result.
+static int refine_report(int n, bool two, const std::vector<double>& h, const PhaseOut& pl,
+                         const PhaseOut& ph, int flags, int rc, int z0_used, zf_result* res,
+                         double* hist, int hist_cap) {
+  const int len = (int)h.size() < hist_cap ? (int)h.size() : hist_cap;
+  for (int i = 0; i < len; ++i) hist[i] = h[i];
+  if ((int)h.size() > hist_cap && hist_cap >= 0 && rc >= 0) flags |= ZF_WARN_HIST_TRUNC;
+  const double fe = two ? ph.err : pl.err;
+  if (res) {
+    res->iters = pl.updates + ph.updates;
+    res->low_evals = pl.evals;
+    res->high_evals = ph.evals;
+    res->hist_len = len;
+    res->flags = flags;
+    res->final_err = fe;
+    res->final_rms = fe / sqrt((double)n);
+    res->status = rc < 0 ? rc : 0;
+    res->z0_used = z0_used;
+  }
+  if (rc < 0) return rc;
+  if (!(fe < 1.0)) {
+    if (res) res->status = ZF_ERR_NOT_CONVERGED;
+    return fail(ZF_ERR_NOT_CONVERGED,
+                "||Z^T S Z - I||_F = %g >= 1: the guess violates ||X0 - I||_2 < 1 or S is not SPD",
+                fe);
+  }
+  g_err.clear();
+  return flags;
+}
+
+// Orders that one team refines in one kernel (team.hip).  Past them an XCD's matrix cores
+// bound the products and launches over the whole chip win.  One kernel against launches:
+// mixed N = 64 155 / 281 us, N = 128 177 / 309, N = 256 244 / 345, N = 320 297 / 379, N = 384 374 /
+// 346; FP64 N = 128 148 / 247, N = 192 197 / 274, N = 256 293 / 308, N = 320 431 / 344.
+// ZF_TEAM_MAX overrides (0: never; tests and tuning).
+static int team_max_order(bool fp64) {
+  const char* env = getenv("ZF_TEAM_MAX");
+  if (env) return std::min(atoi(env), 2048);
+  return fp64 ? 256 : 320;
+}
+
+// Longest wait of a team for its members: 0.2 s (ZF_TEAM_SPIN, in 10 ns ticks, for tests).
+static long long team_spin() {
+  const char* env = getenv("ZF_TEAM_SPIN");
+  return env ? atoll(env) : 20000000ll;
+}
+
+// The whole solve by one team.  Returns 1 when it is done (the report is in w.team), 0 when the
+// team could not run (Z is untouched).
+static int team_refine(Workspace& w, const double* S, const double* Z0, int n, bool fp64,
+                       bool refine, const zf_opts& o, int max_l, int max_h, double* Z,
+                       hipStream_t st) {
+  TeamMat m;
+  memset(&m, 0, sizeof m);
+  m.n = n;
+  m.np = round_up(n, 64);
+  m.s_hi = w.s_hi;
+  m.s_lo = w.s_lo;
+  m.at_hi = w.at_hi;
+  m.at_lo = w.at_lo;
+  m.d_hi = w.d_hi;
+  m.d_lo = w.d_lo;
+  m.q_hi = w.q_hi;
+  m.q_lo = w.q_lo;
+  m.u_hi = w.u_hi;
+  m.u_lo = w.u_lo;
+  for (int b = 0; b < 2; ++b) {
+    m.zr_hi[b] = w.zr_hi[b];
+    m.zr_lo[b] = w.zr_lo[b];
+    m.zc_hi[b] = w.zc_hi[b];
+    m.zc_lo[b] = w.zc_lo[b];
+    m.z32[b] = w.z32[b];
+    m.z64r[b] = w.z64r[b];
+    m.z64c[b] = w.z64c[b];
+  }
+  m.s64 = w.s64;
+  m.a64t = w.a64t;
+  m.d64 = w.d64;
+  m.q64 = w.q64;
+  m.u64 = w.u64;
+  m.partials = w.partials;
+  m.rowsum = w.rowsum;
+  m.S = S;
+  m.Z0 = Z0;
+  m.Z = Z;
+  m.hist = w.team_dev->hist;
+  m.out = &w.team_dev->out;
+  m.ctl = w.team_ctl;
+  TeamCall call;
+  memset(&call, 0, sizeof call);
+  call.order = o.order;
+  call.rule = o.stop;
+  call.max_l = max_l;
+  call.max_h = max_h;
+  call.hist_cap = kTeamHist;
+  call.fp64 = fp64;
+  call.refine = refine;
+  call.setup = 1;
+  series(o.order, call.c);
+  call.spin = team_spin();
+  // A member per 64-wide tile; where FP64 products run too, per 32-wide tile of theirs.  Past
+  // 32 members two share a CU, which only the all-FP64 recursion gains from (N = 256: 330 us
+  // with 32 members, 293 with 64; mixed 244 and 266).
+  const int T = m.np / (fp64 || refine ? 32 : 64);
+  w.team->out.done = 0;
+  HIP_TRY(launch_team_one(m, call, std::min(T * T, fp64 ? kTeamMaxSize : 32), st));
+  HIP_TRY(hipStreamSynchronize(st));
+  return w.team->out.done ? 1 : 0;
+}
+
 static int refine_core(const double* S, const double* Z0, int n, const zf_opts& o, double* Z,
                        zf_result* res, double* hist, int hist_cap, hipStream_t st, bool log) {
   if (!S || !Z) return fail(ZF_ERR_ARG, "S and Z must be non-NULL device pointers");
@@ -954,6 +1085,36 @@ static int refine_core(const double* S, const double* Z0, int n, const zf_opts& 
   ZF_TRY(ws_get(np, need_pairs, use_h || learned, &w, need_f32, refine && hd == AR_EMU,
                 crt_mode));
 
+  const int max_l = o.max_sweeps > 0 ? o.max_sweeps : 100;
+  const int max_h = o.max_refine > 0 ? o.max_refine : 10;
+  std::vector<double> h;
+  int cur = 0;
+  PhaseOut pl, ph;
+  int rc = 0;
+  int z0_used = Z0 ? ZF_Z0_GIVEN : ZF_Z0_SCALED_IDENTITY;
+  int flags = 0;
+  const bool team = (la == AR_X3 || la == AR_F64) && !learned && !log && !g_prof.on &&
+                    (!refine || o.refine == ZF_REFINE_F64_DELTA) && n <= team_max_order(fp64_only) &&
+                    max_l < kTeamHist / 2 && max_h < kTeamHist / 2 - 2;
+  if (team) {
+    const int tr = team_refine(*w, S, Z0, n, fp64_only, refine, o, max_l, max_h, Z, st);
+    if (tr < 0) return tr;
+    if (tr == 1) {
+      const TeamOut& t = w->team->out;
+      h.assign(w->team->hist, w->team->hist + t.hist_len);
+      pl.updates = t.upd_l;
+      pl.evals = t.evals_l;
+      pl.err = t.err_l;
+      ph.updates = t.upd_h;
+      ph.evals = t.evals_h;
+      ph.err = t.err_h;
+      flags = t.flags;
+      if (t.status == ZF_ERR_NONFINITE)
+        rc = fail(ZF_ERR_NONFINITE, "residual norm is not finite at sweep %d", t.hist_len - 1);
+      return refine_report(n, fp64_only || refine, h, pl, ph, flags, rc, z0_used, res, hist, hist_cap);
+    }
+  }
+
   Ctx c;
   c.w = w;
   c.n = n;
@@ -970,21 +1131,17 @@ static int refine_core(const double* S, const double* Z0, int n, const zf_opts& 
   c.log = log;
   const int s_fmt = ar_f16(la) ? 2 : 1;  // split format of S: FP16 or BF16 halves
   series(o.order, c.c);
-  const int max_l = o.max_sweeps > 0 ? o.max_sweeps : 100;
-  const int max_h = o.max_refine > 0 ? o.max_refine : 10;
 
   // setup: operands of S, then Z0
   TraceRange setup_range("zf.setup");
   HIP_TRY(launch_split_pad(S, n, n, np, s_pairs ? w->s_hi : nullptr, s_pairs ? w->s_lo : nullptr,
                            (use_h || learned) ? w->s64 : nullptr,
                            need_f32 ? w->s32 : nullptr, false, s_fmt, st));
-  int z0_used = Z0 ? ZF_Z0_GIVEN : ZF_Z0_SCALED_IDENTITY;
-  int guess_flags = 0;
   if (learned) {
     int lr = learned_guess(c, S, mixed, fp64_only, s_pairs, ar_pm(la), st);
     if (lr < 0) return lr;
     if (lr == 1) z0_used = ZF_Z0_LEARNED;
-    else guess_flags |= ZF_WARN_Z0_FALLBACK;
+    else flags |= ZF_WARN_Z0_FALLBACK;
   }
   if (Z0) {
     HIP_TRY(launch_init_given(Z0, n, np, mixed ? w->z32[0] : nullptr,
@@ -1007,11 +1164,6 @@ static int refine_core(const double* S, const double* Z0, int n, const zf_opts& 
                          w->zc_hi[0], w->zc_lo[0], 1.0f, PAIR_F16));
   setup_range.end();
 
-  std::vector<double> h;
-  int cur = 0;
-  PhaseOut pl, ph;
-  int flags = guess_flags;
-  int rc = 0;
   if (mixed) {
     rc = run_phase(c, la, la, false, o.stop, max_l, cur, h, pl);
     if (rc < 0) goto done;
@@ -1041,32 +1193,7 @@ static int refine_core(const double* S, const double* Z0, int n, const zf_opts& 
 
 done:
   if (g_prof.on) prof_harvest();
-  {
-    const int len = (int)h.size() < hist_cap ? (int)h.size() : hist_cap;
-    for (int i = 0; i < len; ++i) hist[i] = h[i];
-    if ((int)h.size() > hist_cap && hist_cap >= 0 && rc >= 0) flags |= ZF_WARN_HIST_TRUNC;
-    if (res) {
-      res->iters = pl.updates + ph.updates;
-      res->low_evals = pl.evals;
-      res->high_evals = ph.evals;
-      res->hist_len = len;
-      res->flags = flags;
-      res->final_err = (fp64_only || refine) ? ph.err : pl.err;
-      res->final_rms = res->final_err / sqrt((double)n);
-      res->status = rc < 0 ? rc : 0;
-      res->z0_used = z0_used;
-    }
-  }
-  if (rc < 0) return rc;
-  const double fe = (fp64_only || refine) ? ph.err : pl.err;
-  if (!(fe < 1.0)) {
-    if (res) res->status = ZF_ERR_NOT_CONVERGED;
-    return fail(ZF_ERR_NOT_CONVERGED,
-                "||Z^T S Z - I||_F = %g >= 1: the guess violates ||X0 - I||_2 < 1 or S is not SPD",
-                fe);
-  }
-  g_err.clear();
-  return flags;
+  return refine_report(n, fp64_only || refine, h, pl, ph, flags, rc, z0_used, res, hist, hist_cap);
 }
 
 // refine_core under a roctx range, with one ZF_LOG line for the call's result.
