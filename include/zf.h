@@ -178,8 +178,11 @@ int zf_refine_ex(const double* S, const double* Z0, int n, const zf_opts* opts, 
  * launches it and reads the live count once per launch, and kernels of macro-sweeps
  * after every matrix has stopped return at once.  The tile edge per matrix comes from
  * the table of
- * zf_batched_set_tiles / zf_batched_autotune.  Returns the OR of the warnings, or the
- * first failing matrix's error (every result is still filled).
+ * zf_batched_set_tiles / zf_batched_autotune.  A batch whose orders are all at most 512
+ * runs in one kernel instead, each matrix by a team of workgroups of its own, without
+ * lockstep (the same iterates; only the rounding of the residual norms differs), unless
+ * zf_batched_use_graph(0) asks for eager macro-sweeps.  Returns the OR of the warnings, or
+ * the first failing matrix's error (every result is still filled).
  */
 int zf_refine_batched(int count, const double* const* S, const double* const* Z0, const int* n,
                       const zf_opts* opts, double* const* Z, zf_result* res, double* hist,
@@ -199,8 +202,8 @@ int zf_batched_get_tiles(int* max_n, int* tile, int cap);
 int zf_batched_autotune(const int* bucket_n, int nbuckets, int batch, int reps, int* best_tile,
                         double* ms, void* stream);
 
-/* zf_batched_use_graph -- 1 (default): replay the captured macro-sweep graph; 0: launch
- * the same kernels eagerly (for checking the graph). */
+/* zf_batched_use_graph -- 1 (default): replay the captured macro-sweep graph (small orders
+ * run by teams); 0: launch the graph's kernels eagerly for every batch (for checking it). */
 void zf_batched_use_graph(int on);
 
 /* zf_batched_set_graph_sweeps -- macro-sweeps per graph launch: k > 0 (default 8)
@@ -212,7 +215,7 @@ int zf_batched_set_graph_sweeps(int sweeps);
 
 /* zf_batched_last_stats -- of the last zf_refine_batched call: the macro-sweeps in which
  * some matrix was still live, and the number of graph launches (either pointer may be
- * NULL). */
+ * NULL).  After a call run by teams: the sweeps that lockstep would have taken, and 0. */
 int zf_batched_last_stats(int* macro_sweeps, int* graph_launches);
 
 /* zf_batched_release -- free the batched path's cached arena, graph and stream. */

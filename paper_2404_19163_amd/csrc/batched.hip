@@ -44,6 +44,7 @@
 
 #include "zf.h"
 #include "zf_internal.h"
+#include "zf_team.h"
 #include "gemm_tiles.inc"
 
 namespace zf {
@@ -679,6 +680,10 @@ struct BatchState {
   hipStream_t cap = nullptr;
   hipGraphExec_t exec = nullptr;
   std::vector<char> key;  // layout the captured graph was built for
+  // teams: records, report and histories on the device, the same in pinned memory, and the
+  // meeting points (zero between launches)
+  void *team = nullptr, *team_host = nullptr, *team_ctl = nullptr;
+  size_t team_bytes = 0, team_host_bytes = 0, team_ctls = 0;
 };
 static BatchState g_b;
 
@@ -688,6 +693,9 @@ static void batch_release() {
   if (g_b.meta) (void)hipFree(g_b.meta);
   if (g_b.pinned) (void)hipHostFree(g_b.pinned);
   if (g_b.cap) (void)hipStreamDestroy(g_b.cap);
+  if (g_b.team) (void)hipFree(g_b.team);
+  if (g_b.team_host) (void)hipHostFree(g_b.team_host);
+  if (g_b.team_ctl) (void)hipFree(g_b.team_ctl);
   g_b = BatchState();
 }
 
@@ -746,7 +754,9 @@ static void make_plan(int count, const int* n, bool with64, Plan& P) {
     const int T64 = M.np / 64;
     M.ftiles_sym = T64 * (T64 + 1) / 2;
     M.pbase = P.partials;
-    P.partials += std::max(M.tiles_sym, M.ftiles_sym);
+    // a team's FP64 tiles are 32 wide, and its set-up keeps np row sums there
+    const int T32 = M.np / 32;
+    P.partials += std::max(std::max(M.tiles_sym, T32 * (T32 + 1) / 2), M.np);
     P.max_etiles = std::max(P.max_etiles, (M.np / kET) * (M.np / kET));
     const size_t e = (size_t)M.np * M.np;
     bytes += 16 * align256(e * 2) + 2 * align256(e * 4) + (with64 ? 7 * align256(e * 8) : 0);
@@ -855,9 +865,172 @@ static hipError_t macro_sweep(const Launch& L, hipStream_t st) {
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// refinement by teams (team.hip)
+// ---------------------------------------------------------------------------
+// A batch whose orders are all at most this is refined by teams, each matrix by its own, with
+// no step that waits for the other matrices.  Teams against macro-sweeps: 8 matrices of N =
+// 64 to 200 256 / 557 us, 48 of 48 to 300 0.81 / 1.57 ms, 160 of 32 to 128 0.57 / 0.94 ms, 128 of
+// 64 to 600 3.9 / 4.2 ms, 16 of 200 to 900 2.52 / 2.56 ms; 512 of 64 to 1024, where 128-wide tiles
+// over the whole chip pay, 31 / 26 ms.
+// ZF_TEAM_BATCH_MAX overrides (0: never; tests and tuning).
+static int team_batch_max() {
+  const char* env = getenv("ZF_TEAM_BATCH_MAX");
+  return env ? std::min(atoi(env), 8192) : 512;
+}
+
+// Workgroups of the grid: every matrix gets a team in proportion to its 32-wide tiles, such
+// that a small batch fills the chip (two workgroups a CU) and a large one queues for it,
+// and goes to the XCD with the least work so far, largest first.  A team's members are
+// consecutive in their XCD's share of the grid, which is dispatched in order, so a team that
+// waits for its last members waits only for teams that are complete.
+static void team_slots(const std::vector<BMat>& mats, std::vector<TeamSlot>& slots) {
+  const int count = (int)mats.size();
+  std::vector<int> order(count);
+  double tiles = 0.0;
+  for (int m = 0; m < count; ++m) {
+    order[m] = m;
+    tiles += (mats[m].np / 32) * (double)(mats[m].np / 32);
+  }
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return mats[a].np > mats[b].np; });
+  // 32-wide tiles a member: what fills 512 places, at most 8 (512 matrices of N = 64 to 256 take
+  // 4.0 ms with 4, 3.7 with 8, 4.6 with 16)
+  const double per = std::min(std::max(tiles / 512.0, 1.0), 8.0);
+  double load[8] = {};
+  std::vector<TeamSlot> run[8];
+  for (int m : order) {
+    const double T = mats[m].np / 32;
+    const int size = std::min(std::max((int)(T * T / per + 0.5), 1), 32);
+    int x = 0;
+    for (int k = 1; k < 8; ++k)
+      if (load[k] < load[x]) x = k;
+    load[x] += T * T * (T + 4.0);
+    for (int r = 0; r < size; ++r) run[x].push_back(TeamSlot{m, (short)r, (short)size});
+  }
+  size_t longest = 0;
+  for (const auto& r : run) longest = std::max(longest, r.size());
+  slots.assign(8 * longest, TeamSlot{-1, 0, 0});
+  for (int x = 0; x < 8; ++x)
+    for (size_t j = 0; j < run[x].size(); ++j) slots[8 * j + x] = run[x][j];
+}
+
+static int grow_pinned(void** p, size_t* cap, size_t need) {
+  if (*cap >= need) return 0;
+  if (*p) (void)hipHostFree(*p);
+  *p = nullptr;
+  *cap = 0;
+  if (hipHostMalloc(p, need, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+    return set_error(ZF_ERR_NOMEM, "hipHostMalloc(%zu bytes) for the batch failed", need);
+  }
+  *cap = need;
+  return 0;
+}
+
+// Refine the planned matrices by teams.  setup: from S and Z0 (scaled identity where null);
+// otherwise buffer 0 holds Z0.  outs and hists (count x hcap) are left in pinned
+// memory; an out that is not done means that its team gave up and wrote no Z.
+static int run_teams(const std::vector<BMat>& mats, double* partials, const double* const* S,
+                     const double* const* Z0, double* const* Z, const TeamCall& call, int hcap,
+                     hipStream_t st, const TeamOut** outs, const double** hists) {
+  const int count = (int)mats.size();
+  std::vector<TeamSlot> slots;
+  team_slots(mats, slots);
+  const size_t o_slots = align256(sizeof(TeamMat) * count);
+  const size_t up = align256(o_slots + sizeof(TeamSlot) * slots.size());
+  const size_t o_hist = align256(up + sizeof(TeamOut) * count);
+  const size_t total = align256(o_hist + 8 * (size_t)count * hcap);
+  int rc = grow(&g_b.team, &g_b.team_bytes, total);
+  if (rc < 0) return rc;
+  rc = grow_pinned(&g_b.team_host, &g_b.team_host_bytes, total);
+  if (rc < 0) return rc;
+  if (g_b.team_ctls < (size_t)count) {
+    size_t have = 0;
+    if (g_b.team_ctl) (void)hipFree(g_b.team_ctl);
+    g_b.team_ctl = nullptr;
+    g_b.team_ctls = 0;
+    rc = grow(&g_b.team_ctl, &have, sizeof(TeamCtl) * count);
+    if (rc < 0) return rc;
+    BHIP_TRY(hipMemset(g_b.team_ctl, 0, sizeof(TeamCtl) * count));
+    g_b.team_ctls = count;
+  }
+  char* d = (char*)g_b.team;
+  char* h = (char*)g_b.team_host;
+  TeamMat* tm = (TeamMat*)h;
+  for (int m = 0; m < count; ++m) {
+    const BMat& M = mats[m];
+    TeamMat& t = tm[m];
+    memset(&t, 0, sizeof t);
+    t.n = M.n;
+    t.np = M.np;
+    t.s_hi = M.s_hi;
+    t.s_lo = M.s_lo;
+    for (int b = 0; b < 2; ++b) {
+      t.zr_hi[b] = M.zr_hi[b];
+      t.zr_lo[b] = M.zr_lo[b];
+      t.zc_hi[b] = M.zc_hi[b];
+      t.zc_lo[b] = M.zc_lo[b];
+      t.z32[b] = M.z32[b];
+      t.z64r[b] = M.z64r[b];
+      t.z64c[b] = M.z64c[b];
+    }
+    t.at_hi = M.at_hi;
+    t.at_lo = M.at_lo;
+    t.d_hi = M.d_hi;
+    t.d_lo = M.d_lo;
+    t.q_hi = M.q_hi;
+    t.q_lo = M.q_lo;
+    t.s64 = M.s64;
+    t.a64t = M.a64t;
+    t.d64 = M.d64;
+    t.partials = t.rowsum = partials + M.pbase;
+    t.S = S[m];
+    t.Z0 = Z0 ? Z0[m] : nullptr;
+    t.Z = Z[m];
+    t.hist = (double*)(d + o_hist) + (size_t)m * hcap;
+    t.out = (TeamOut*)(d + up) + m;
+    t.ctl = (TeamCtl*)g_b.team_ctl + m;
+  }
+  memcpy(h + o_slots, slots.data(), sizeof(TeamSlot) * slots.size());
+  BHIP_TRY(hipMemcpyAsync(d, h, up, hipMemcpyHostToDevice, st));
+  BHIP_TRY(launch_team_many((const TeamMat*)d, (const TeamSlot*)(d + o_slots), (int)slots.size(),
+                            call, st));
+  BHIP_TRY(hipMemcpyAsync(h + up, d + up, total - up, hipMemcpyDeviceToHost, st));
+  BHIP_TRY(hipStreamSynchronize(st));
+  *outs = (const TeamOut*)(h + up);
+  *hists = (const double*)(h + o_hist);
+  return 0;
+}
+
+// One matrix's outcome into its result record and history; its status.
+static int report(const BMat& M, bool with64, int hist_cap, const double* from, double* hist,
+                  zf_result* res, int* flags_out) {
+  const int len = std::min(M.hist_len, hist_cap);
+  for (int k = 0; k < len; ++k) hist[k] = from[k];
+  int flags = M.flags;
+  if (M.hist_len > hist_cap) flags |= ZF_WARN_HIST_TRUNC;
+  const double fe = with64 ? M.err_h : M.err_l;
+  int status = M.status;
+  if (status == 0 && !(fe < 1.0)) status = ZF_ERR_NOT_CONVERGED;
+  if (res) {
+    res->iters = M.upd_l + M.upd_h;
+    res->low_evals = M.evals_l;
+    res->high_evals = M.evals_h;
+    res->hist_len = len;
+    res->flags = flags;
+    res->final_err = fe;
+    res->final_rms = fe / sqrt((double)M.n);
+    res->status = status;
+    res->z0_used = M.z0_used;
+  }
+  *flags_out = flags;
+  return status;
+}
+
 static int batched_impl(int count, const double* const* S, const double* const* Z0, const int* n,
                         const zf_opts& o, double* const* Z, zf_result* res, double* hist,
-                        int hist_cap, hipStream_t st) {
+                        int hist_cap, hipStream_t st, bool allow_teams = true) {
   if (count <= 0 || count > 65535 || !S || !Z || !n)
     return set_error(ZF_ERR_ARG, "bad batch arguments (count must be in 1..65535)");
   if (o.order != 2) return set_error(ZF_ERR_ARG, "the batched path supports order 2 (got %d)", o.order);
@@ -881,6 +1054,38 @@ static int batched_impl(int count, const double* const* S, const double* const* 
   const int max_l = o.max_sweeps > 0 ? o.max_sweeps : 100;
   const int max_h = o.max_refine > 0 ? o.max_refine : 10;
   const int hcap = std::max(hist_cap, 1);
+  // Results and histories (count x hcap) to the caller; the call's return code.  Matrices of
+  // `redo` (ascending) ran in a call of their own, which left their results in r2 and h2.
+  auto finish = [&](const std::vector<BMat>& out, const double* h, const std::vector<int>& redo,
+                    const std::vector<zf_result>& r2, const std::vector<double>& h2) -> int {
+    int ret = 0, first_err = 0, first_m = -1;
+    size_t next = 0;
+    for (int m = 0; m < count; ++m) {
+      int flags = 0, status = 0;
+      double* hm = hist ? hist + (size_t)m * hist_cap : nullptr;
+      if (next < redo.size() && redo[next] == m) {
+        const zf_result& r = r2[next];
+        for (int k = 0; k < r.hist_len; ++k) hm[k] = h2[next * hist_cap + k];
+        if (res) res[m] = r;
+        flags = r.flags;
+        status = r.status;
+        ++next;
+      } else {
+        status = report(out[m], with64, hist_cap, h + (size_t)m * hcap, hm, res ? res + m : nullptr,
+                        &flags);
+      }
+      if (status < 0 && first_err == 0) {
+        first_err = status;
+        first_m = m;
+      }
+      ret |= flags;
+    }
+    if (first_err < 0)
+      return set_error(first_err, "matrix %d of the batch failed (status %d); see the results",
+                       first_m, first_err);
+    clear_error();
+    return ret;
+  };
 
   int dev = 0;
   BHIP_TRY(hipGetDevice(&dev));
@@ -945,6 +1150,76 @@ static int batched_impl(int count, const double* const* S, const double* const* 
   char* mb = (char*)g_b.meta;
   for (int m = 0; m < count; ++m) P.mats[m].hist = (double*)(mb + o_hist) + (size_t)m * hcap;
 
+  TeamCall call;
+  memset(&call, 0, sizeof call);
+  call.order = o.order;
+  call.rule = o.stop;
+  call.max_l = max_l;
+  call.max_h = max_h;
+  call.hist_cap = hcap;
+  call.refine = with64;
+  call.c[0] = 1.0;
+  call.c[1] = 0.5;
+  call.c[2] = 0.375;
+  call.spin = team_spin_ticks();
+  const bool teams = allow_teams && g_use_graph && max_n <= team_batch_max();
+  // the batch by teams; matrices whose team gave up (their Z is untouched) by macro-sweeps
+  auto by_teams = [&](std::vector<BMat>& out) -> int {
+    const TeamOut* to = nullptr;
+    const double* th = nullptr;
+    const int rc = run_teams(out, (double*)(mb + o_part), S, Z0, Z, call, hcap, st, &to, &th);
+    if (rc < 0) return rc;
+    int low = 0, high = 0;
+    std::vector<int> redo;
+    for (int m = 0; m < count; ++m) {
+      BMat& M = out[m];
+      const TeamOut& t = to[m];
+      if (!t.done) {
+        redo.push_back(m);
+        continue;
+      }
+      M.status = t.status;
+      M.flags |= t.flags;
+      M.upd_l = t.upd_l;
+      M.upd_h = t.upd_h;
+      M.evals_l = t.evals_l;
+      M.evals_h = t.evals_h;
+      M.err_l = t.err_l;
+      M.err_h = t.err_h;
+      M.hist_len = t.hist_len;
+      low = std::max(low, t.evals_l);
+      high = std::max(high, t.evals_h);
+    }
+    std::vector<zf_result> r2(redo.size());
+    std::vector<double> h2(redo.size() * (size_t)hist_cap);
+    if (!redo.empty()) {
+      const std::vector<double> hs(th, th + (size_t)count * hcap);  // the call below reuses it
+      std::vector<const double*> s2, z2;
+      std::vector<double*> o2;
+      std::vector<int> n2;
+      for (int m : redo) {
+        s2.push_back(S[m]);
+        z2.push_back(Z0 ? Z0[m] : nullptr);
+        o2.push_back(Z[m]);
+        n2.push_back(n[m]);
+      }
+      const int rc2 = batched_impl((int)redo.size(), s2.data(), z2.data(), n2.data(), o, o2.data(),
+                                   r2.data(), h2.data(), hist_cap, st, false);
+      bool told = rc2 >= 0;
+      for (const zf_result& r : r2) told |= r.status < 0;
+      if (!told) return rc2;  // the call itself failed, not a matrix of it
+      return finish(out, hs.data(), redo, r2, h2);
+    }
+    g_last_sweeps = low + high;
+    g_last_launches = 0;
+    return finish(out, th, redo, r2, h2);
+  };
+  if (teams && n_learn == 0) {
+    call.setup = 1;
+    std::vector<BMat> out = P.mats;
+    return by_teams(out);
+  }
+
   std::vector<const void*> ps(count), pz0(count), pz(count);
   for (int m = 0; m < count; ++m) {
     ps[m] = S[m];
@@ -1001,6 +1276,12 @@ static int batched_impl(int count, const double* const* S, const double* const* 
                        d_stats, d_coef);
   }
   hipLaunchKernelGGL(b_init_kernel, eg, dim3(256), 0, st, d_mats, d_Z0, d_S, d_g, d_coef);
+  if (teams) {  // learned guesses: set up above, what the acceptance decided read back
+    std::vector<BMat> out(count);
+    BHIP_TRY(hipMemcpyAsync(out.data(), d_mats, sizeof(BMat) * count, hipMemcpyDeviceToHost, st));
+    BHIP_TRY(hipStreamSynchronize(st));
+    return by_teams(out);
+  }
   hipLaunchKernelGGL(b_reset_kernel, dim3(1), dim3(64), 0, st, (int*)(mb + o_rem), count);
   BHIP_TRY(hipGetLastError());
 
@@ -1095,38 +1376,7 @@ static int batched_impl(int count, const double* const* S, const double* const* 
     return set_error(ZF_ERR_HIP, "batched refinement did not finish in %d macro-sweeps",
                      launched);
 
-  int ret = 0, first_err = 0, first_m = -1;
-  for (int m = 0; m < count; ++m) {
-    const BMat& M = out[m];
-    const int len = std::min(M.hist_len, hist_cap);
-    for (int k = 0; k < len; ++k) hist[(size_t)m * hist_cap + k] = h[(size_t)m * hcap + k];
-    int flags = M.flags;
-    if (M.hist_len > hist_cap) flags |= ZF_WARN_HIST_TRUNC;
-    const double fe = with64 ? M.err_h : M.err_l;
-    int status = M.status;
-    if (status == 0 && !(fe < 1.0)) status = ZF_ERR_NOT_CONVERGED;
-    if (res) {
-      res[m].iters = M.upd_l + M.upd_h;
-      res[m].low_evals = M.evals_l;
-      res[m].high_evals = M.evals_h;
-      res[m].hist_len = len;
-      res[m].flags = flags;
-      res[m].final_err = fe;
-      res[m].final_rms = fe / sqrt((double)M.n);
-      res[m].status = status;
-      res[m].z0_used = M.z0_used;
-    }
-    if (status < 0 && first_err == 0) {
-      first_err = status;
-      first_m = m;
-    }
-    ret |= flags;
-  }
-  if (first_err < 0)
-    return set_error(first_err, "matrix %d of the batch failed (status %d); see the results",
-                     first_m, first_err);
-  clear_error();
-  return ret;
+  return finish(out, h.data(), {}, {}, {});
 }
 
 // ---------------------------------------------------------------------------

@@ -962,7 +962,7 @@ static int team_max_order(bool fp64) {
 }
 
 // Longest wait of a team for its members: 0.2 s (ZF_TEAM_SPIN, in 10 ns ticks, for tests).
-static long long team_spin() {
+long long team_spin_ticks() {
   const char* env = getenv("ZF_TEAM_SPIN");
   return env ? atoll(env) : 20000000ll;
 }
@@ -1019,7 +1019,7 @@ static int team_refine(Workspace& w, const double* S, const double* Z0, int n, b
   call.refine = refine;
   call.setup = 1;
   series(o.order, call.c);
-  call.spin = team_spin();
+  call.spin = team_spin_ticks();
   // A member per 64-wide tile; where FP64 products run too, per 32-wide tile of theirs.  Past
   // 32 members two share a CU, which only the all-FP64 recursion gains from (N = 256: 330 us
   // with 32 members, 293 with 64; mixed 244 and 266).

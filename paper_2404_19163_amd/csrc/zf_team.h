@@ -51,6 +51,8 @@ struct TeamCall {
   long long spin;  // longest wait for a team, in ticks of the 100 MHz clock
 };
 
+long long team_spin_ticks();  // TeamCall::spin of a call (zf_api.hip)
+
 // One matrix, its team on one XCD.
 hipError_t launch_team_one(const TeamMat& m, const TeamCall& call, int size, hipStream_t st);
 // first[b] of the grid's workgroups: b runs as rank[b] of matrix mat[b]'s team of size[b]

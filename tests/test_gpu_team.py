@@ -79,3 +79,65 @@ def test_not_finite(zf):
     with pytest.raises(zf.ZFError) as e:
         zf.refine(S)
     assert e.value.code == zf.ERR_NONFINITE
+
+
+ORDERS = [1, 40, 64, 65, 100, 129, 192, 200, 256, 300, 385, 512]
+
+
+def _batch(seed, orders=ORDERS):
+    return [torch.from_numpy(inputs.overlap_gaussian(n, 1.0 + 0.02 * i, seed + i)).cuda()
+            for i, n in enumerate(orders)]
+
+
+def _same_batch(a, b):
+    assert a.rc == b.rc
+    for x, y in zip(a.results, b.results):
+        assert (x.status, x.flags) == (y.status, y.flags)
+        _same(x, y)
+
+
+@pytest.mark.parametrize("guess,ref,stop", [("identity", "f64_delta", "ratio"),
+                                            ("learned", "f64_delta", "ratio"),
+                                            ("identity", "off", "monotone")])
+def test_batch_equals_macro_sweeps(zf, monkeypatch, guess, ref, stop):
+    """Teams and lockstep macro-sweeps; matrix 3 starts from a given guess."""
+    if guess == "learned":
+        zf.mlp_set_params([0.0] * zf.N_PARAMS)
+        zf.mlp_set_norm([0.0] * 8, [1.0] * 8, [2.2, -2.0, 0.9], [1.0] * 3)
+    S = _batch(1)
+    Z0 = [None] * len(S)
+    Z0[3] = torch.eye(65, dtype=torch.float64, device="cuda") / S[3].abs().sum(1).max().sqrt()
+    Z0[3][0, 1] += 1e-3
+    kw = dict(guess=guess, refine=ref, stop=stop, max_sweeps=20)
+    monkeypatch.setenv("ZF_TEAM_BATCH_MAX", "0")
+    a = zf.refine_batched(S, Z0, **kw)
+    monkeypatch.setenv("ZF_TEAM_BATCH_MAX", "512")
+    _same_batch(a, zf.refine_batched(S, Z0, **kw))
+    assert zf.batched_last_stats()[1] == 0  # no graph was launched
+
+
+@pytest.mark.parametrize("guess", ["identity", "learned"])
+def test_batch_gives_up_waiting(zf, monkeypatch, guess):
+    """Teams without time to wait: their matrices, aliased guesses included, run by
+    macro-sweeps, the one-member teams' do not."""
+    zf.mlp_set_params([0.0] * zf.N_PARAMS)
+    zf.mlp_set_norm([0.0] * 8, [1.0] * 8, [2.2, -2.0, 0.9], [1.0] * 3)
+    S = _batch(7)
+    Z0 = [torch.eye(s.shape[0], dtype=torch.float64, device="cuda") / s.abs().sum(1).max().sqrt()
+          if i % 2 else None for i, s in enumerate(S)]
+    monkeypatch.setenv("ZF_TEAM_BATCH_MAX", "0")
+    a = zf.refine_batched(S, Z0, guess=guess)
+    monkeypatch.setenv("ZF_TEAM_BATCH_MAX", "512")
+    for spin in ("0", "300", "20000000"):
+        monkeypatch.setenv("ZF_TEAM_SPIN", spin)
+        out = [torch.empty_like(s) if z is None else z.clone() for s, z in zip(S, Z0)]
+        z0 = [None if z is None else o for z, o in zip(Z0, out)]
+        _same_batch(a, zf.refine_batched(S, z0, guess=guess, out=out))
+
+
+def test_batch_error_isolated(zf):
+    S = _batch(11, [100, 90, 300])
+    S[1][2, 3] = S[1][3, 2] = float("nan")
+    out = zf.refine_batched(S, raise_on_error=False)
+    assert out.rc == zf.ERR_NONFINITE
+    assert [r.status for r in out.results] == [0, zf.ERR_NONFINITE, 0]
