@@ -34,8 +34,8 @@ namespace zf {
 template <int BM, int BN, int WM, int WN, bool SYM, int PM, int NS, int OCC>
 __global__ void __launch_bounds__(WM* WN * 64, OCC)
     gemm_x3_kernel(const u16* __restrict__ Ahi, const u16* __restrict__ Alo, int lda,
-                   const u16* __restrict__ Bhi, const u16* __restrict__ Blo, int ldb, int K,
-                   int tiles_n, int gm, EpiParams ep, int ksa, int ksb) {
+                   const u16* __restrict__ Bhi, const u16* __restrict__ Blo, int ldb, int M,
+                   int N, int K, int tiles_n, int gm, EpiParams ep, int ksa, int ksb) {
   __shared__ __attribute__((aligned(16))) u16 lds[x3_lds(BM, BN, PM, NS, WM * WN)];
   __shared__ double red[WM * WN];
   if (ep.gate && *ep.gate) return;
@@ -43,8 +43,16 @@ __global__ void __launch_bounds__(WM* WN * 64, OCC)
   int ti, tj;
   tile_coords(bid, tiles_n, SYM, ti, tj, gm);
   const int mode = SYM ? (ti == tj ? 2 : 1) : 0;
-  x3_tile<BM, BN, WM, WN, PM, NS>(Ahi, Alo, lda, Bhi, Blo, ldb, K, ti * BM, tj * BN, mode, ep,
-                                  tile_index(ti, tj, tiles_n, SYM), lds, red, ksa, ksb);
+  int m0 = ti * BM, n0 = tj * BN, m_lo = 0, n_lo = 0;
+  if constexpr (BM == 192) {  // may not divide the order: the last tiles move back inside
+    m_lo = m0;
+    n_lo = n0;
+    m0 = m0 < M - BM ? m0 : M - BM;
+    n0 = n0 < N - BN ? n0 : N - BN;
+  }
+  x3_tile<BM, BN, WM, WN, PM, NS>(Ahi, Alo, lda, Bhi, Blo, ldb, K, m0, n0, mode, ep,
+                                  tile_index(ti, tj, tiles_n, SYM), lds, red, ksa, ksb, m_lo,
+                                  n_lo);
 }
 
 // FP32 matrix-core GEMM ("single"): f32_mainloop + the shared epilogue.
@@ -99,38 +107,48 @@ static bool dims_ok(int M, int N, int K, bool sym) {
 }
 
 static int grid_blocks(int M, int N, int t, bool sym) {
-  const int tm = M / t, tn = N / t;
+  const int tm = (M + t - 1) / t, tn = (N + t - 1) / t;
   return sym ? tm * (tm + 1) / 2 : tm * tn;
 }
 
-// Tile edge of a launch.  Per flop the 256-wide tile is the fastest and the 64-wide the
-// slowest (operand traffic), but each needs a grid that fills the 256 CUs, where a 256- or
-// 128-wide block takes a CU for itself:
-//  - 256 from 160 tiles on, from 128 on in symmetric mode.  Full N = 3584 (196 tiles) 237 us
-//    against 275 with 128-wide tiles, N = 3072 (144) 195 / 181.  Symmetric N = 5120 (210)
-//    353 / 435; at N = 4096 (136) one launch takes 261 / 250, but under sustained load, when
-//    the clock follows the energy used, the mixed solve takes 11.0 ms against 11.2.
-//  - else 128 from 192 tiles on.  Full N = 1792 (196) 43 us against 48 with 64-wide tiles,
-//    N = 1536 (144) 37 / 35; symmetric N = 2560 (210) 66 / 76, N = 2304 (171) 59 / 58.
-//  - but not where 128-wide tiles would leave a second round mostly empty while 64-wide
-//    ones fill the chip evenly: symmetric N = 3072 (300 tiles) 135 us against 118, N = 3584
-//    (406) 162 / 214.
-//  - else 64.
-// (Overlap matrices, means over a mixed solve.)  ZF_X3_TILE / ZF_X3_SYM_TILE (64, 128 or
-// 256) force the edge when it divides (tuning).
+// Forced tile edge (tuning), 0 for none: ZF_X3_TILE / ZF_X3_SYM_TILE where it divides.
+static int forced_edge(int M, int N, bool sym) {
+  const char* env = getenv(sym ? "ZF_X3_SYM_TILE" : "ZF_X3_TILE");
+  const int want = env ? atoi(env) : 0;
+  return (want == 64 || want == 128 || want == 256) && M % want == 0 && N % want == 0 ? want : 0;
+}
+
+// Tile edge of a launch.  Per flop the 256-wide tile is the fastest (operand traffic), but
+// it, the 192- and the 128-wide one take a CU for themselves, so the number of full rounds
+// over the 256 CUs decides.  Estimated time of a launch in rounds of 256-wide tiles:
+//   256: 1 per round; 192: 0.6; 128: 0.34 (0.25 of the work); 64: 0.11 (1 + tiles per CU),
+//   as up to four of these share a CU.
+// The 192-wide tile need not divide the order.  Per round and column of the contraction,
+// measured over N = 1024 to 5120 (overlap matrices, mixed solve): 256 58-65 ns, 192 34-42,
+// 128 18-21, 64 14 + 7 per tile and CU; the low ends are for rounds that leave CUs idle,
+// where the clock stays higher.  Times per launch by edge, 256 / 192 / 128 wide, us:
+//   full N = 3072 179 / 125 / 168, N = 3584 218 / 250 / 257, N = 4096 266 / 311 / 321,
+//   N = 4352 504 / 445 / 408, N = 5120 615 / 576 / 643;
+//   symmetric N = 3072 154 / 103 / 111, N = 4096 210 / 170 / 221, N = 5120 314 / 377 / 383.
+// 64 against 128 wide: full N = 1024 14 / 22, N = 1536 33 / 32; symmetric N = 1536 25 / 32,
+// N = 2304 52 / 48.
 int x3_tile_edge(int M, int N, bool sym) {
   const char* env = getenv(sym ? "ZF_X3_SYM_TILE" : "ZF_X3_TILE");
-  if (env) {
-    const int want = atoi(env);
-    if ((want == 64 || want == 128 || want == 256) && M % want == 0 && N % want == 0) return want;
-  }
-  if (M % 256 == 0 && N % 256 == 0 && grid_blocks(M, N, 256, sym) >= (sym ? 128 : 160))
-    return 256;
-  if (M % 128 == 0 && N % 128 == 0) {
-    const int t = grid_blocks(M, N, 128, sym);
-    if (t >= 192 && !(sym && t > 256 && t <= 352)) return 128;
-  }
-  return 64;
+  if (env && atoi(env) == 192 && M >= 192 && N >= 192) return 192;
+  if (const int want = forced_edge(M, N, sym)) return want;
+  auto rounds = [&](int t) { return (grid_blocks(M, N, t, sym) + 255) / 256; };
+  int edge = 64;
+  double best = 0.11 * (1 + rounds(64));
+  auto offer = [&](int t, double cost) {
+    if (cost < best) {
+      best = cost;
+      edge = t;
+    }
+  };
+  if (M % 128 == 0 && N % 128 == 0) offer(128, 0.34 * rounds(128));
+  if (M >= 192 && N >= 192) offer(192, 0.6 * rounds(192));
+  if (M % 256 == 0 && N % 256 == 0) offer(256, 1.0 * rounds(256));
+  return edge;
 }
 
 int x3_blocks(int M, int N, bool sym) { return grid_blocks(M, N, x3_tile_edge(M, N, sym), sym); }
@@ -157,8 +175,9 @@ int f64_tile_edge(int M, int N, bool sym) {
 // covers 4 x 8 tiles, 12 operand panels instead of 18); ZF_TILE_GROUP overrides.
 static int tile_group(int M, int t) {
   const char* env = getenv("ZF_TILE_GROUP");
-  const int gm = env ? atoi(env) : 4;
-  return (gm > 1 && (M / t) % gm == 0) ? gm : 1;
+  const int gm = env ? atoi(env) : 4, tm = (M + t - 1) / t;
+  if (!env && tm % 4 != 0) return tm % 3 == 0 ? 3 : tm % 5 == 0 ? 5 : tm % 2 == 0 ? 2 : 1;
+  return (gm > 1 && tm % gm == 0) ? gm : 1;
 }
 
 // Band height of the symmetric-grid tile order: 4 (a run of 17 of the 136 tiles of
@@ -181,11 +200,11 @@ static void x3_launch(const u16* Ahi, const u16* Alo, int lda, const u16* Bhi, c
                       hipStream_t st, int ksa, int ksb) {
   if (sym)
     hipLaunchKernelGGL((gemm_x3_kernel<BM, BN, WM, WN, true, PM, NS, OCC>), dim3(blocks),
-                       dim3(WM * WN * 64), 0, st, Ahi, Alo, lda, Bhi, Blo, ldb, K, N / BN, sym_group(), ep,
+                       dim3(WM * WN * 64), 0, st, Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, (N + BN - 1) / BN, sym_group(), ep,
                        ksa, ksb);
   else
     hipLaunchKernelGGL((gemm_x3_kernel<BM, BN, WM, WN, false, PM, NS, OCC>), dim3(blocks),
-                       dim3(WM * WN * 64), 0, st, Ahi, Alo, lda, Bhi, Blo, ldb, K, N / BN,
+                       dim3(WM * WN * 64), 0, st, Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, (N + BN - 1) / BN,
                        tile_group(M, BM), ep, ksa, ksb);
 }
 
@@ -217,6 +236,9 @@ static void x3_dispatch(const u16* Ahi, const u16* Alo, int lda, const u16* Bhi,
                         const EpiParams& ep, hipStream_t st, int ksa, int ksb) {
   if (tile == 256)
     x3_launch<256, 256, 2, 4, PM, 2, 1>(Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, sym, blocks, ep, st,
+                                        ksa, ksb);
+  else if (tile == 192)  // 4 waves of 96 x 96, loads two stages ahead
+    x3_launch<192, 192, 2, 2, PM, 3, 1>(Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, sym, blocks, ep, st,
                                         ksa, ksb);
   else if (tile == 128)  // 8 waves of 32 x 64, one block per CU, loads three stages ahead
     x3_launch<128, 128, 4, 2, PM, 4, 1>(Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, sym, blocks, ep, st,
@@ -256,9 +278,17 @@ hipError_t launch_gemm_x3(const u16* Ahi, const u16* Alo, int lda, const u16* Bh
   return hipGetLastError();
 }
 
-// FP32 tiles follow the BF16x3 choice (same tile bodies and occupancy).
-int f32_tile_edge(int M, int N, bool sym) { return x3_tile_edge(M, N, sym); }
-int f32_blocks(int M, int N, bool sym) { return x3_blocks(M, N, sym); }
+// FP32 tile edge: these tiles' main loop needs larger grids than the pairs' (256 from 128
+// tiles, 128 from 192).
+int f32_tile_edge(int M, int N, bool sym) {
+  if (const int want = forced_edge(M, N, sym)) return want;
+  if (M % 256 == 0 && N % 256 == 0 && grid_blocks(M, N, 256, sym) >= 128) return 256;
+  if (M % 128 == 0 && N % 128 == 0 && grid_blocks(M, N, 128, sym) >= 192) return 128;
+  return 64;
+}
+int f32_blocks(int M, int N, bool sym) {
+  return grid_blocks(M, N, f32_tile_edge(M, N, sym), sym);
+}
 
 hipError_t launch_gemm_f32(const float* A, int lda, const float* B, int ldb, int M, int N, int K,
                            bool sym, const EpiParams& ep, hipStream_t st) {

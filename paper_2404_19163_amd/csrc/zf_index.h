@@ -73,11 +73,11 @@ __host__ __device__ inline int tile_index(int ti, int tj, int tiles_n, bool sym)
 
 // Blocks are dispatched round-robin over the 8 XCDs (block b runs on XCD b % 8).
 // Renumber so that each XCD receives a contiguous run of tiles, which then share
-// operand rows in that XCD's L2.  A permutation of [0, nblocks) when nblocks is a
-// multiple of 8, the identity otherwise.
+// operand rows in that XCD's L2; the first nblocks % 8 XCDs hold one tile more.  A
+// permutation of [0, nblocks).
 __host__ __device__ inline int xcd_remap(int bid, int nblocks) {
-  if (nblocks % 8 != 0) return bid;
-  return (bid % 8) * (nblocks / 8) + bid / 8;
+  const int x = bid % 8, r = nblocks % 8;
+  return x * (nblocks / 8) + (x < r ? x : r) + bid / 8;
 }
 
 // ---------------------------------------------------------------------------

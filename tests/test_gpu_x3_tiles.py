@@ -60,3 +60,27 @@ def test_symmetric_epilogue(zf, monkeypatch, tile, n):
     bound = abs(be) * (3 * 2.0 ** -16 + 3 * k * 2.0 ** -24 * 1.02) * absx * 1.01 + 1e-14
     assert np.all(np.abs(C - ref) <= bound)
     assert s == pytest.approx(np.sum(C * C), rel=1e-12)
+
+
+@pytest.mark.parametrize("prec", ["bf16x3", "bf16", "fp16x3"])
+@pytest.mark.parametrize("n,k,sym", [(190, 40, True), (200, 128, False), (200, 40, True),
+                                     (330, 180, True), (580, 250, False), (580, 70, True),
+                                     (1100, 40, False), (2048, 390, True)])
+def test_192_wide_edge_agrees_bitwise(zf, monkeypatch, prec, n, k, sym):
+    """The 192-wide tile need not divide the padded order: its last row and column of tiles
+    move back inside the matrix and leave the other tiles' blocks alone.  Remainders of 0, 64
+    and 128, contractions from the shortest (64), with D, both layouts and the norm, each
+    element counted once."""
+    rng = np.random.default_rng(n)
+    A = torch.from_numpy(rng.standard_normal((n, k))).cuda()
+    B = A if sym else torch.from_numpy(rng.standard_normal((n, k))).cuda()
+    D = rng.standard_normal((n, n))
+    D = torch.from_numpy(D + D.T).cuda()
+    out = {}
+    for tile in ("64", "192"):
+        monkeypatch.setenv("ZF_X3_TILE", tile)
+        monkeypatch.setenv("ZF_X3_SYM_TILE", tile)
+        out[tile] = zf.t_gemm(prec, A, B, sym=sym, alpha=0.5, D=D, beta=-1.5, gamma=0.25,
+                              kblocked=True)
+    assert torch.equal(out["192"][0], out["64"][0])
+    assert out["192"][1] == pytest.approx(out["64"][1], rel=1e-12)
