@@ -150,24 +150,31 @@ __global__ void __launch_bounds__(256) crt_residue_kernel(const double* __restri
 // ---------------------------------------------------------------------------
 // one int8 product per modulus, reduced to its residue
 // ---------------------------------------------------------------------------
-// 256 x 256 output tiles, 8 waves of 128 x 64, the BF16 tiles' direct-to-LDS
-// mainloop in its int8 mode with a 4-stage ring.  One block per (tile, modulus): the products of the L
+// 256 x 256 output tiles, 4 waves of 128 x 128, the BF16 tiles' direct-to-LDS main loop in
+// its int8 mode with a 3-stage ring.  One block per (tile, modulus): the products of the L
 // moduli are independent, so a grid of L times the tile count fills the chip even
 // when the tiles alone would not (the symmetric N = 4096 product: 136 tiles, 1904
-// blocks).  The block's int32 sums are reduced to rho_l in [0, m_l) and stored as bytes
-// of plane l.  Symmetric mode computes the tiles on or above the diagonal only (the
+// blocks).  The block's int32 sums are reduced to rho_l in [0, m_l) and stored in plane l,
+// the residues of rows 4 g .. 4 g + 3 of a column as one word (g np + column): whole
+// 128-byte lines straight from the accumulators, and one load a modulus in the
+// reconstruction.  Symmetric mode computes the tiles on or above the diagonal only (the
 // reconstruction mirrors).  Blocks are numbered modulus-major, so consecutive blocks
 // (renumbered to run together on one XCD) share that modulus's operand panels.
+//
+// Bound by the matrix cores and the clock they sustain.  With 8 waves of 128 x 64 the
+// fragment reads and direct loads took 124 of the LDS's 128 bytes per cycle; a wave of
+// 128 x 128 reads two thirds as much.  L = 14, full / symmetric: N = 4096 804 -> 745 /
+// 477 -> 431 us, N = 3072 365 -> 346 / 262 -> 219 us (2.6 POP/s full).
 template <bool SYM>
-__global__ void __launch_bounds__(512)
+__global__ void __launch_bounds__(256, 1)
     crt_gemm_kernel(const u16* __restrict__ A, const u16* __restrict__ B, int ld16,
                     size_t plane16, int K16, int tiles_n, int gm, CrtConsts cc,
                     unsigned char* __restrict__ rho, size_t plane, int np,
                     const int* __restrict__ gate) {
   if (gate && *gate) return;
-  constexpr int BM = 256, BN = 256, WM = 2, WN = 4, NS = 4;
+  constexpr int BM = 256, BN = 256, WM = 2, WN = 2, NS = 3;
   using C = X3Cfg<BM, BN, 32, WM, WN>;
-  // single-product stages of (BM + BN) 32 elements: a 4-stage ring, three stages loading
+  // single-product stages of (BM + BN) 32 elements
   __shared__ __attribute__((aligned(16))) u16 lds[NS * x3_stage(BM, BN, PM_I8)];
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   const int ntiles = gridDim.x / cc.L;
@@ -189,22 +196,30 @@ __global__ void __launch_bounds__(512)
     const int md = cc.mod[l];
     const float inv = 1.0f / (float)md;
     // a lane holds rows 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32 of each
-    // 32 x 32 block
-    unsigned char* out = rho + (size_t)l * plane + (size_t)(m0 + wm * C::WTM + 4 * (lane >> 5)) * np +
-                         n0 + wn * C::WTN + (lane & 31);
+    // 32 x 32 block: four residues of a column make one word of the plane
+    unsigned* out = reinterpret_cast<unsigned*>(rho + (size_t)l * plane) +
+                    (size_t)((m0 + wm * C::WTM) / 4 + (lane >> 5)) * np + n0 + wn * C::WTN +
+                    (lane & 31);
 #pragma unroll
     for (int a = 0; a < C::FM; ++a)
 #pragma unroll
       for (int b = 0; b < C::FN; ++b) {
         const i32x16 iv = __builtin_bit_cast(i32x16, acc[a][b]);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          // |c| <= K 128^2 <= 2^28: the single-precision quotient is off by at most
-          // one, so c - m q lies in (-m, m) and one step brings it into [0, m)
-          const int c = iv[r];
-          int ri = c - md * (int)rintf((float)c * inv);
-          if (ri < 0) ri += md;
-          out[(size_t)(a * 32 + 8 * (r >> 2) + (r & 3)) * np + b * 32] = (unsigned char)ri;
+        for (int g = 0; g < 4; ++g) {
+          unsigned w = 0;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            // |c| <= K 128^2 <= 2^28: the single-precision quotient, rounded to an integer
+            // in the low bits of 1.5 2^23 + q, is off by at most one, so c - m q lies in
+            // (-m, m); of it and of it plus m, the one in [0, m) is the least as unsigned
+            const int c = iv[4 * g + k];
+            const int t = __builtin_bit_cast(int, fmaf((float)c, inv, 12582912.0f));
+            const int r = c - __mul24(t, md) + (md << 22);  // t's low 24 bits: 2^22 + q
+            const unsigned u = (unsigned)r, v = (unsigned)(r + md);
+            w |= (u < v ? u : v) << (8 * k);
+          }
+          out[(size_t)(a * 8 + 2 * g) * np + b * 32] = w;
         }
       }
   }
@@ -213,14 +228,14 @@ __global__ void __launch_bounds__(512)
 // ---------------------------------------------------------------------------
 // reconstruction and epilogue
 // ---------------------------------------------------------------------------
-// C' from the L residues of one element (see the file comment), in units of
+// C' from byte q of L words of residues (see the file comment), in units of
 // 2^(e_i + f_j - 2 beta).
 template <int L>
-__device__ __forceinline__ double crt_value(const unsigned char (&res)[L], const CrtConsts& cc) {
+__device__ __forceinline__ double crt_value(const unsigned (&res)[L], int q4, const CrtConsts& cc) {
   double t0 = 0.0, t1 = 0.0, t2 = 0.0;
 #pragma unroll
   for (int l = 0; l < L; ++l) {
-    const double r = (double)res[l];
+    const double r = (double)((res[l] >> (8 * q4)) & 0xffu);
     t0 = fma(r, cc.w[l][0], t0);  // every partial sum is an integer below 2^53: exact
     t1 = fma(r, cc.w[l][1], t1);
     t2 = fma(r, cc.w[l][2], t2);
@@ -240,8 +255,10 @@ __device__ __forceinline__ double crt_value(const unsigned char (&res)[L], const
 // One 64 x 64 element tile per block (symmetric mode: tiles on or above the
 // diagonal, walked row by row, each element of the upper triangle formed once and
 // mirrored by the epilogue); each thread takes groups of 4 consecutive rows of one
-// column, the FP64 epilogue's unit, and requests the group's 4 L residues before
-// using any of them.
+// column, the FP64 epilogue's unit, whose residues are one word a modulus, and requests
+// the group's L words before using any of them.  Bound by memory (L + 8 to 20 bytes an
+// element) and the FP64 recombination: N = 4096, L = 14, byte loads -> words 145 -> 113 us
+// full, 134 -> 114 us symmetric.
 template <int L>
 __global__ void __launch_bounds__(256)
     crt_reconstruct_kernel(const unsigned char* __restrict__ rho, size_t plane, int np,
@@ -259,11 +276,10 @@ __global__ void __launch_bounds__(256)
 #pragma unroll 1
   for (int g = 0; g < 4; ++g) {
     const int row0 = ti * 64 + 4 * ((threadIdx.x >> 6) + 4 * g);
-    unsigned char res[4][L];
+    unsigned res[L];  // a word: the residues of rows row0 .. row0 + 3
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int l = 0; l < L; ++l) res[q][l] = rho[l * plane + (size_t)(row0 + q) * np + col];
+    for (int l = 0; l < L; ++l)
+      res[l] = reinterpret_cast<const unsigned*>(rho + l * plane)[(size_t)(row0 >> 2) * np + col];
     double v[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -274,7 +290,7 @@ __global__ void __launch_bounds__(256)
       } else if (er == kCrtBad || ec == kCrtBad) {
         v[q] = __builtin_nan("");
       } else {
-        v[q] = ldexp(crt_value<L>(res[q], cc), er + ec - 2 * cc.beta);
+        v[q] = ldexp(crt_value<L>(res, q, cc), er + ec - 2 * cc.beta);
       }
     }
     epi_group(ep, row0, col, v, mode, nsum);
@@ -378,10 +394,10 @@ hipError_t launch_crt_product(const signed char* A, const int* ea, const signed 
   const u16* b16 = reinterpret_cast<const u16*>(B);
   const size_t plane16 = (size_t)np * np / 2, plane = (size_t)np * np;
   if (sym)
-    hipLaunchKernelGGL(crt_gemm_kernel<true>, dim3(blocks), dim3(512), 0, st, a16, b16, np / 2,
+    hipLaunchKernelGGL(crt_gemm_kernel<true>, dim3(blocks), dim3(256), 0, st, a16, b16, np / 2,
                        plane16, np / 2, tiles, 1, cc, rho, plane, np, ep.gate);
   else
-    hipLaunchKernelGGL(crt_gemm_kernel<false>, dim3(blocks), dim3(512), 0, st, a16, b16, np / 2,
+    hipLaunchKernelGGL(crt_gemm_kernel<false>, dim3(blocks), dim3(256), 0, st, a16, b16, np / 2,
                        plane16, np / 2, tiles, tiles % 4 == 0 ? 4 : 1, cc, rho, plane, np,
                        ep.gate);
   hipError_t e = hipGetLastError();
