@@ -295,7 +295,7 @@ __global__ void __launch_bounds__(256)
     }
     epi_group(ep, row0, col, v, mode, nsum);
   }
-  if (ep.partials) block_norm_store<256>(nsum, ep.partials, tile_index(ti, tj, T, sym != 0), red);
+  if (ep.partials) block_norm_store<256>(nsum, ep, tile_index(ti, tj, T, sym != 0), red);
 }
 
 // ---------------------------------------------------------------------------

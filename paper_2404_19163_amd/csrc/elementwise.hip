@@ -22,7 +22,9 @@ static inline int grid_for(size_t work, int block) {
 // ---------------------------------------------------------------------------
 __global__ void split_pad_kernel(const double* __restrict__ src, int n, int ld_src, int np,
                                  u16* __restrict__ hi, u16* __restrict__ lo,
-                                 double* __restrict__ c64, float* __restrict__ c32, int fmt) {
+                                 double* __restrict__ c64, float* __restrict__ c32, int fmt,
+                                 int* __restrict__ clear) {
+  if (clear && blockIdx.x == 0 && threadIdx.x < 4) clear[threadIdx.x] = 0;
   const size_t total = (size_t)np * np;
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (size_t)gridDim.x * blockDim.x) {
@@ -44,11 +46,11 @@ __global__ void split_pad_kernel(const double* __restrict__ src, int n, int ld_s
 
 hipError_t launch_split_pad(const double* src, int n, int ld_src, int np, u16* hi, u16* lo,
                             double* copy64, float* copy32, bool transpose_copy, int fmt,
-                            hipStream_t st) {
+                            hipStream_t st, int* clear) {
   (void)transpose_copy;
   const size_t total = (size_t)np * np;
   hipLaunchKernelGGL(split_pad_kernel, dim3(grid_for(total, 256)), dim3(256), 0, st, src, n, ld_src,
-                     np, hi, lo, copy64, copy32, fmt);
+                     np, hi, lo, copy64, copy32, fmt, clear);
   return hipGetLastError();
 }
 
@@ -315,42 +317,6 @@ __global__ void norm_finalize_kernel(const double* __restrict__ partials, int co
 hipError_t launch_norm_finalize(const double* partials, int count, double* out, hipStream_t st,
                                 double div) {
   hipLaunchKernelGGL(norm_finalize_kernel, dim3(1), dim3(256), 0, st, partials, count, out, div);
-  return hipGetLastError();
-}
-
-// Err of the sweep (the same fixed-order sum as norm_finalize_kernel), then the stop
-// test of Algorithm 2 (Sec. IV.A) on the device; see launch_norm_decide.
-__global__ void norm_decide_kernel(const double* __restrict__ partials, int count, int it,
-                                   int rule, int pw, int* gate, double* state, double* box) {
-  __shared__ double red[256];
-  if (*gate) return;
-  double s = 0.0;
-  for (int i = threadIdx.x; i < count; i += 256) s += partials[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x != 0) return;
-  const double err = sqrt(red[0]);
-  int code = 0;
-  if (!isfinite(err)) {
-    code = 2;
-  } else if (it > 0) {
-    const double prev = state[0];
-    code = rule == 1 ? (err >= prev) : (err > pow(prev, (double)pw));
-  }
-  if (code) *gate = 1;
-  else state[0] = err;
-  box[0] = err;
-  box[1] = (double)code;
-}
-
-hipError_t launch_norm_decide(const double* partials, int count, int it, int rule, int pw,
-                              int* gate, double* state, double* box, hipStream_t st) {
-  hipLaunchKernelGGL(norm_decide_kernel, dim3(1), dim3(256), 0, st, partials, count, it, rule, pw,
-                     gate, state, box);
   return hipGetLastError();
 }
 

@@ -22,6 +22,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -205,13 +206,13 @@ struct Workspace {
   int *cr_es = nullptr, *cr_ez = nullptr, *cr_ea = nullptr;
   unsigned char* cr_rho = nullptr;
   // scalars
-  double *partials = nullptr, *err_dev = nullptr, *rowsum = nullptr, *g_dev = nullptr;
+  double *partials = nullptr, *rowsum = nullptr, *g_dev = nullptr;
   double *gscr = nullptr, *cg = nullptr;  // learned-guess scratch (8192) and coefficients (8)
   float* feats = nullptr;
-  double* host_err = nullptr;  // pinned
-  // device-side stop test: the phase's gate (nonzero once it stopped), the previous
-  // Err, and a ring of kBoxSlots {Err, decision} pairs the host reads (pinned, coherent,
-  // written by the device; box_dev is its device address)
+  // device-side stop test: each phase's gate (nonzero once it stopped; [0] and [1]) and the
+  // count of finished blocks ([2]), the previous Err, and a ring of kBoxSlots words the host
+  // reads (pinned, coherent, written by the device; box_dev is its device address;
+  // kBoxEmpty until then)
   int* gate = nullptr;
   double* prev_dev = nullptr;
   double *box = nullptr, *box_dev = nullptr;
@@ -221,13 +222,14 @@ struct Workspace {
   TeamReport *team = nullptr, *team_dev = nullptr;
 };
 constexpr int kBoxSlots = 8;
+constexpr unsigned long long kBoxEmpty = ~0ull;
+constexpr int kGateWords = 4;
 
 static Workspace g_ws;
 
 static void ws_free(Workspace& w) {
   for (void* p : w.allocs) hipFree(p);
   w.allocs.clear();
-  if (w.host_err) hipHostFree(w.host_err);
   if (w.box) hipHostFree(w.box);
   if (w.team) hipHostFree(w.team);
   int dev = w.device;
@@ -266,20 +268,16 @@ static int ws_build(Workspace& w, int dev, int np, bool x3, bool f64, bool f32, 
   const size_t m = (size_t)np * np;
   const int tiles = max_blocks(np, np);
   ZF_TRY(ws_alloc(w, &w.partials, tiles));
-  ZF_TRY(ws_alloc(w, &w.err_dev, 8));
   ZF_TRY(ws_alloc(w, &w.rowsum, np));
   ZF_TRY(ws_alloc(w, &w.g_dev, 8));
   ZF_TRY(ws_alloc(w, &w.gscr, 8192));
   ZF_TRY(ws_alloc(w, &w.cg, 8));
   ZF_TRY(ws_alloc(w, &w.feats, 64));
-  if (hipHostMalloc((void**)&w.host_err, 8 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    w.host_err = nullptr;
-    return fail(ZF_ERR_NOMEM, "hipHostMalloc of the pinned norm word failed");
-  }
-  ZF_TRY(ws_alloc(w, &w.gate, 2));
+  ZF_TRY(ws_alloc(w, &w.gate, kGateWords));
+  if (hipMemset(w.gate, 0, kGateWords * sizeof(int)) != hipSuccess)
+    return fail(ZF_ERR_HIP, "hipMemset of the gates failed");
   ZF_TRY(ws_alloc(w, &w.prev_dev, 1));
-  if (hipHostMalloc((void**)&w.box, 2 * kBoxSlots * sizeof(double),
+  if (hipHostMalloc((void**)&w.box, kBoxSlots * sizeof(double),
                     hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
       hipHostGetDevicePointer((void**)&w.box_dev, w.box, 0) != hipSuccess) {
     (void)hipGetLastError();
@@ -543,6 +541,8 @@ struct Ctx {
   bool crt_s_ready = false;  // S's residues are in the workspace (once per call)
   bool crt_first = false;    // only the refinement phase's first evaluation uses AR_CRT
   bool log = false;         // ZF_LOG: one JSON line per residual evaluation
+  int phases = 0;           // phases run so far (at most two: one gate each)
+  StopTest stop{};          // of the next residual evaluation (none: counter null)
 };
 
 static void series(int m, double* c) {
@@ -551,19 +551,46 @@ static void series(int m, double* c) {
   for (int k = 1; k <= m; ++k) c[k] = c[k - 1] * (2.0 * k - 1.0) / (2.0 * k);
 }
 
-// Frobenius norm from the partials of the last GEMM2 (count = its block count) -> host
-static int fetch_err(Ctx& c, int count, double* err) {
-  HIP_TRY(launch_norm_finalize(c.w->partials, count, c.w->err_dev, c.st));
-  HIP_TRY(hipMemcpyAsync(c.w->host_err, c.w->err_dev, sizeof(double), hipMemcpyDeviceToHost, c.st));
-  HIP_TRY(hipStreamSynchronize(c.st));
-  *err = c.w->host_err[0];
+// Prepares mailbox slot k for the stop test of the next residual evaluation.
+static void arm_stop(Ctx& c, int k, int* gate, int it, int rule, int pw) {
+  Workspace& w = *c.w;
+  *reinterpret_cast<volatile unsigned long long*>(w.box + k % kBoxSlots) = kBoxEmpty;
+  c.stop = StopTest{reinterpret_cast<unsigned*>(w.gate) + 2, gate, w.prev_dev,
+                    w.box_dev + k % kBoxSlots, it, rule, pw};
+}
+
+// Waits until the device has filled mailbox slot k: Err and 0 (go on), 1 (stop) or 2 (not
+// finite).  The host reads the word itself, as an event recorded for it would cost the
+// stream 5 us of idle time, and a query of the stream about as much: that is left to waits
+// long past any sweep's time, so that a failed launch ends them.
+static int wait_box(Ctx& c, int k, double* err, int* code) {
+  const double* slot = c.w->box + k % kBoxSlots;
+  const volatile unsigned long long* box = reinterpret_cast<const volatile unsigned long long*>(slot);
+  using clock = std::chrono::steady_clock;
+  auto asked = clock::now();
+  unsigned long long word;
+  for (unsigned spin = 1; (word = *box) == kBoxEmpty; ++spin) {
+    if (spin % 1024 != 0 || clock::now() - asked < std::chrono::milliseconds(50)) continue;
+    const hipError_t e = hipStreamQuery(c.st);
+    asked = clock::now();
+    if (e == hipErrorNotReady) {
+      (void)hipGetLastError();  // not a failure that a later launch should report
+      continue;
+    }
+    HIP_TRY(e);
+    if (*box == kBoxEmpty) return fail(ZF_ERR_HIP, "a residual evaluation left no stop test");
+  }
+  double v;
+  memcpy(&v, &word, sizeof v);
+  *code = !std::isfinite(v) ? 2 : std::signbit(v) ? 1 : 0;
+  *err = std::fabs(v);
   return 0;
 }
 
 // Residual products of Z[cur] in arithmetic `da`, leaving delta where the correction
-// in arithmetic `ca` reads it (BF16 pair, FP32 or FP64) and its norm partials (their
-// count in *blocks).  Every launch reads `gate` (nullptr: none).
-static int delta_products(Ctx& c, Arith da, Arith ca, int cur, const int* gate, int* blocks_out) {
+// in arithmetic `ca` reads it (BF16 pair, FP32 or FP64), its norm partials and the stop
+// test c.stop.  Every launch reads `gate` (nullptr: none).
+static int delta_products(Ctx& c, Arith da, Arith ca, int cur, const int* gate) {
   Workspace& w = *c.w;
   const int np = c.np;
   EpiParams e1 = epi0(np, c.n), e2 = epi0(np, c.n);
@@ -571,11 +598,11 @@ static int delta_products(Ctx& c, Arith da, Arith ca, int cur, const int* gate, 
   e2.beta = -1.0;
   e2.gamma = 1.0;
   e2.partials = w.partials;
+  e2.stop = c.stop;
   if (ca != da && ar_pairs(ca)) {  // FP64 delta, BF16-pair correction
     e2.ohi = e2.othi = w.d_hi;
     e2.olo = e2.otlo = w.d_lo;
   }
-  int blocks = 0;
   if (ar_pairs(da)) {
     const int pm = ar_pm(da);
     const int fmt = ar_f16(da) ? PAIR_F16 : PAIR_BF16;
@@ -590,7 +617,6 @@ static int delta_products(Ctx& c, Arith da, Arith ca, int cur, const int* gate, 
       e2.olo = e2.otlo = w.d_lo;
     }
     ZF_TRY(gemm_x3(w.zc_hi[cur], w.zc_lo[cur], w.at_hi, w.at_lo, np, true, e2, c.st, pm));
-    blocks = x3_blocks(np, np, true);
   } else if (da == AR_EMU) {  // A^T = Z^T S and Z^T A, both emulated, A^T kept in FP64
     const int s = c.oz_slices;
     if (!c.oz_s_ready) {
@@ -603,7 +629,6 @@ static int delta_products(Ctx& c, Arith da, Arith ca, int cur, const int* gate, 
     HIP_TRY(launch_oz_slice(w.a64t, np, s, w.oz_a, w.oz_ea, c.st, gate));
     e2.o64 = e2.ot64 = w.d64;
     ZF_TRY(gemm_oz(w.oz_z, w.oz_ez, w.oz_a, w.oz_ea, np, s, true, e2, c.st));
-    blocks = oz_blocks(np, true);
   } else if (da == AR_CRT) {  // the same two products through residues, A^T kept in FP64
     const int L = c.crt_moduli;
     if (!c.crt_s_ready) {
@@ -616,21 +641,17 @@ static int delta_products(Ctx& c, Arith da, Arith ca, int cur, const int* gate, 
     HIP_TRY(launch_crt_residues(w.a64t, np, L, c.n, w.cr_a, w.cr_ea, c.st, gate));
     e2.o64 = e2.ot64 = w.d64;
     ZF_TRY(gemm_crt(w.cr_z, w.cr_ez, w.cr_a, w.cr_ea, np, L, c.n, true, w.cr_rho, e2, c.st));
-    blocks = crt_blocks(np, true);
   } else if (da == AR_F32) {
     e1.o32 = w.a32t;
     ZF_TRY(gemm_f32(w.zc32[cur], w.s32, np, false, e1, c.st));
     e2.o32 = e2.ot32 = w.dl32;
     ZF_TRY(gemm_f32(w.zc32[cur], w.a32t, np, true, e2, c.st));
-    blocks = f32_blocks(np, np, true);
   } else {
     e1.o64 = w.a64t;
     ZF_TRY(gemm_f64(w.z64c[cur], w.s64, np, false, e1, c.st));
     e2.o64 = e2.ot64 = w.d64;
     ZF_TRY(gemm_f64(w.z64c[cur], w.a64t, np, true, e2, c.st));
-    blocks = f64_blocks(np, np, true);
   }
-  *blocks_out = blocks;
   return 0;
 }
 
@@ -648,9 +669,11 @@ static int delta_f16_split(Ctx& c, Arith da, double err) {
 
 // Residual evaluation of Z[cur] with Err returned to the host (one synchronization).
 static int delta_eval(Ctx& c, Arith da, Arith ca, int cur, double* err) {
-  int blocks = 0;
-  ZF_TRY(delta_products(c, da, ca, cur, nullptr, &blocks));
-  ZF_TRY(fetch_err(c, blocks, err));
+  int code = 0;
+  arm_stop(c, 0, nullptr, 0, 0, 1);
+  ZF_TRY(delta_products(c, da, ca, cur, nullptr));
+  HIP_TRY(hipStreamSynchronize(c.st));
+  ZF_TRY(wait_box(c, 0, err, &code));
   return delta_f16_split(c, da, *err);
 }
 
@@ -764,7 +787,7 @@ struct PhaseOut {
 };
 
 // One phase of Algorithm 2: evaluate, stop test, update, ping-pong.  The stop test
-// runs on the device (launch_norm_decide) and the host queues one sweep ahead: the
+// runs on the device (StopTest) and the host queues one sweep ahead: the
 // update of sweep it and the evaluation of sweep it + 1 are launched before the host
 // reads sweep it's decision, and if that decision was to stop, the gate it set makes
 // every one of those launches return at once (the buffer of the previous iterate is
@@ -779,46 +802,27 @@ static int run_phase(Ctx& c, Arith da, Arith ca, bool high, int stop_rule, int m
   Workspace& w = *c.w;
   const bool ahead = !ar_f16(da);
   const int pw = c.order + 1;
+  int* gate = w.gate + c.phases++;
   auto eval_arith = [&](int it) { return (high && it == 0 && c.crt_first) ? AR_CRT : da; };
   // residual products of sweep it on buffer b, then its device-side stop test
   auto enqueue_eval = [&](int it, int b) -> int {
     TraceRange r("zf.residual_eval");
-    int blocks = 0;
-    ZF_TRY(delta_products(c, eval_arith(it), ca, b, w.gate, &blocks));
-    HIP_TRY(launch_norm_decide(w.partials, blocks, it, stop_rule == ZF_STOP_MONOTONE ? 1 : 0, pw,
-                               w.gate, w.prev_dev, w.box_dev + 2 * (it % kBoxSlots), c.st));
-    return 0;
+    arm_stop(c, it, gate, it, stop_rule == ZF_STOP_MONOTONE ? 1 : 0, pw);
+    return delta_products(c, eval_arith(it), ca, b, gate);
   };
-  HIP_TRY(hipMemsetAsync(w.gate, 0, sizeof(int), c.st));
-  hipEvent_t ev[2] = {nullptr, nullptr};
-  HIP_TRY(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming));
-  if (hipEventCreateWithFlags(&ev[1], hipEventDisableTiming) != hipSuccess) {
-    (void)hipEventDestroy(ev[0]);
-    return fail(ZF_ERR_HIP, "hipEventCreate failed");
-  }
-  struct EvGuard {
-    hipEvent_t* e;
-    ~EvGuard() {
-      (void)hipEventDestroy(e[0]);
-      (void)hipEventDestroy(e[1]);
-    }
-  } guard{ev};
   double prev = 0.0;
   ZF_TRY(enqueue_eval(0, cur));
-  HIP_TRY(hipEventRecord(ev[0], c.st));
   for (int it = 0;; ++it) {
     const bool capped = it >= max_updates;
     const size_t spec = g_prof.pending.size();  // timed launches queued ahead start here
     if (ahead && !capped) {  // queued before the decision of sweep it is known
       TraceRange r("zf.update");
-      ZF_TRY(update(c, da, ca, high, cur, w.gate));
+      ZF_TRY(update(c, da, ca, high, cur, gate));
       ZF_TRY(enqueue_eval(it + 1, cur ^ 1));
-      HIP_TRY(hipEventRecord(ev[(it + 1) & 1], c.st));
     }
-    HIP_TRY(hipEventSynchronize(ev[it & 1]));
-    const volatile double* box = w.box + 2 * (it % kBoxSlots);
-    const double err = box[0];
-    const int code = (int)box[1];
+    double err = 0.0;
+    int code = 0;
+    ZF_TRY(wait_box(c, it, &err, &code));
     out.evals++;
     hist.push_back(err);
     if (c.log)
@@ -850,9 +854,8 @@ static int run_phase(Ctx& c, Arith da, Arith ca, bool high, int stop_rule, int m
     if (!ahead) {  // FP16 halves: delta's scaled split, then the update and next evaluation
       ZF_TRY(delta_f16_split(c, eval_arith(it), err));
       TraceRange r("zf.update");
-      ZF_TRY(update(c, da, ca, high, cur, w.gate));
+      ZF_TRY(update(c, da, ca, high, cur, gate));
       ZF_TRY(enqueue_eval(it + 1, cur ^ 1));
-      HIP_TRY(hipEventRecord(ev[(it + 1) & 1], c.st));
     }
     cur ^= 1;
     prev = err;
@@ -1136,7 +1139,7 @@ static int refine_core(const double* S, const double* Z0, int n, const zf_opts& 
   TraceRange setup_range("zf.setup");
   HIP_TRY(launch_split_pad(S, n, n, np, s_pairs ? w->s_hi : nullptr, s_pairs ? w->s_lo : nullptr,
                            (use_h || learned) ? w->s64 : nullptr,
-                           need_f32 ? w->s32 : nullptr, false, s_fmt, st));
+                           need_f32 ? w->s32 : nullptr, false, s_fmt, st, w->gate));
   if (learned) {
     int lr = learned_guess(c, S, mixed, fp64_only, s_pairs, ar_pm(la), st);
     if (lr < 0) return lr;
@@ -1192,6 +1195,7 @@ static int refine_core(const double* S, const double* Z0, int n, const zf_opts& 
   HIP_TRY(hipStreamSynchronize(st));
 
 done:
+  if (rc < 0) (void)hipStreamSynchronize(st);  // launches queued ahead, on the call's workspace
   if (g_prof.on) prof_harvest();
   return refine_report(n, fp64_only || refine, h, pl, ph, flags, rc, z0_used, res, hist, hist_cap);
 }

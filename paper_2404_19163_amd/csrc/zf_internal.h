@@ -153,6 +153,21 @@ __host__ __device__ inline size_t kb_offset(int r, int k, int ld) {
 // the same matrices for both, and the kernel writes the upper triangle normally
 // and mirrors it.
 // ---------------------------------------------------------------------------
+// The stop test of one sweep, run by the block of the residual product that finishes last:
+// Err from the norm partials, then the rule of Algorithm 2 against the previous Err
+// (state[0]): rule 1 (monotone) stops when Err >= prev, rule 0 (ratio) when Err > prev^pw.
+// *box, one word of mapped, coherent host memory, receives Err, with the sign bit set for a
+// stop (never all ones: a NaN is the positive quiet one); a stop or a non-finite Err sets
+// *gate (unless null), which every later launch of the phase reads and then does nothing,
+// this one included.  counter is 0 between launches.
+struct StopTest {
+  unsigned* counter;
+  int* gate;
+  double* state;
+  double* box;
+  int it, rule, pw;
+};
+
 struct EpiParams {
   double alpha, beta, gamma;
   int n_valid;
@@ -173,6 +188,7 @@ struct EpiParams {
   int pair_fmt;      // PAIR_BF16 / PAIR_F16: format of dhi/dlo and of every pair output
   int kb;            // 16-bit pairs in the K-blocked layout (kb_offset)
   const int* gate;   // non-null and nonzero: the launch does nothing (a stopped phase)
+  StopTest stop;     // counter non-null (partials too; one tile per block): run it
 };
 
 // Launchers (return hipSuccess or the launch error).  All dimensions must be
@@ -232,7 +248,7 @@ int crt_blocks(int np, bool sym);
 // Elementwise / reduction kernels (elementwise.hip)
 hipError_t launch_split_pad(const double* src, int n, int ld_src, int np, u16* hi, u16* lo,
                             double* copy64, float* copy32, bool transpose_copy, int fmt,
-                            hipStream_t st);
+                            hipStream_t st, int* clear = nullptr);  // clear: 4 words set to 0
 hipError_t launch_split_flat(const double* src, int64_t count, u16* hi, u16* lo, int fmt,
                              hipStream_t st);
 hipError_t launch_row_abs_max(const double* S, int n, int ld, double* row_sums, double* g_out,
@@ -254,14 +270,6 @@ hipError_t launch_unpad_f32(const float* src, int np, int n, double* dst, hipStr
 // out[0] = sqrt(sum of the partials) / div (div = 1: the Frobenius norm itself)
 hipError_t launch_norm_finalize(const double* partials, int count, double* out, hipStream_t st,
                                 double div = 1.0);
-// The stop test of one sweep on the device: Err from the partials, then the rule of
-// Algorithm 2 against the previous Err (state[0]): rule 1 (monotone) stops when Err >=
-// prev, rule 0 (ratio) when Err > prev^pw.  box[0] = Err, box[1] = 0 (go on), 1 (stop)
-// or 2 (Err not finite); a stop or a non-finite Err sets *gate, which every later
-// launch of the phase reads and then does nothing, this one included.  box may be
-// host memory (mapped, coherent).
-hipError_t launch_norm_decide(const double* partials, int count, int it, int rule, int pw,
-                              int* gate, double* state, double* box, hipStream_t st);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 
 // Tracing (zf_api.hip).
