@@ -556,7 +556,7 @@ static void arm_stop(Ctx& c, int k, int* gate, int it, int rule, int pw) {
   Workspace& w = *c.w;
   *reinterpret_cast<volatile unsigned long long*>(w.box + k % kBoxSlots) = kBoxEmpty;
   c.stop = StopTest{reinterpret_cast<unsigned*>(w.gate) + 2, gate, w.prev_dev,
-                    w.box_dev + k % kBoxSlots, it, rule, pw};
+                    w.box_dev + k % kBoxSlots, it, rule, pw, nullptr, 1.0};
 }
 
 // Waits until the device has filled mailbox slot k: Err and 0 (go on), 1 (stop) or 2 (not
@@ -1276,9 +1276,7 @@ int zf_residual(const double* S, const double* Z, int n, double* rms, void* stre
   c.st = st;
   c.keep_pairs = false;
   series(2, c.c);
-  HIP_TRY(launch_split_pad(S, n, n, np, nullptr, nullptr, w->s64, nullptr, false, 1, st));
-  HIP_TRY(launch_init_given(Z, n, np, nullptr, w->z64r[0], w->z64c[0], w->zr_hi[0], w->zr_lo[0],
-                            nullptr, nullptr, st));
+  HIP_TRY(launch_stage_residual(S, Z, n, np, w->s64, w->z64c[0], w->gate, st));
   double e = 0.0;
   ZF_TRY(delta_eval(c, AR_F64, AR_F64, 0, &e));
   if (g_prof.on) prof_harvest();
@@ -1291,14 +1289,14 @@ int zf_residual(const double* S, const double* Z, int n, double* rms, void* stre
 // zf_residual_noalloc: zf_residual's products on a fixed device array
 // ---------------------------------------------------------------------------
 // Layout (doubles): padded S | Z^T | A^T = Z^T S (each kNoAllocNp^2, row-major with
-// ld = np for the padded order np of the call) | norm partials.  Every call
-// overwrites what it reads before reading it, so nothing needs clearing; calls that
-// overlap on one GPU share the array and race.
+// ld = np for the padded order np of the call) | norm partials | count of the blocks that
+// have finished.  Every call overwrites what it reads before reading it, so nothing needs
+// clearing beforehand; calls that overlap on one GPU share the array and race.
 constexpr int kNoAllocMaxN = 1024;
 constexpr int kNoAllocNp = 1024;  // pad_order(kNoAllocMaxN)
 constexpr size_t kNoAllocMat = (size_t)kNoAllocNp * kNoAllocNp;
 constexpr int kNoAllocParts = (kNoAllocNp / 32) * (kNoAllocNp / 32);  // max_blocks(np, np)
-static __device__ __align__(256) double scratch[3 * kNoAllocMat + kNoAllocParts];
+static __device__ __align__(256) double scratch[3 * kNoAllocMat + kNoAllocParts + 2];
 
 // Device address of `scratch` on each device, looked up once per device with that
 // device current (host code uses these, never the array's own name).
@@ -1337,16 +1335,17 @@ int zf_residual_noalloc(const double* S, const double* Z, int n, double* rms_dev
   double* zc = base + kNoAllocMat;
   double* at = base + 2 * kNoAllocMat;
   double* parts = base + 3 * kNoAllocMat;
-  HIP_TRY(launch_split_pad(S, n, n, np, nullptr, nullptr, s64, nullptr, false, 1, st));
-  HIP_TRY(launch_init_given(Z, n, np, nullptr, nullptr, zc, nullptr, nullptr, nullptr, nullptr, st));
+  int* words = reinterpret_cast<int*>(parts + kNoAllocParts);
+  HIP_TRY(launch_stage_residual(S, Z, n, np, s64, zc, words, st));
   EpiParams e1 = epi0(np, n), e2 = epi0(np, n);
   e1.o64 = at;  // A^T = Z^T S
   e2.beta = -1.0;  // delta = I - Z^T A, only its norm partials are kept
   e2.gamma = 1.0;
   e2.partials = parts;
+  e2.stop = StopTest{reinterpret_cast<unsigned*>(words), nullptr, nullptr, nullptr, 0, 0, 1,
+                     rms_dev, sqrt((double)n)};
   HIP_TRY(launch_gemm_f64(zc, np, s64, np, np, np, np, false, e1, st));
   HIP_TRY(launch_gemm_f64(zc, np, at, np, np, np, np, true, e2, st));
-  HIP_TRY(launch_norm_finalize(parts, f64_blocks(np, np, true), rms_dev, st, sqrt((double)n)));
   g_err.clear();
   return 0;
 }

@@ -166,6 +166,8 @@ struct StopTest {
   double* state;
   double* box;
   int it, rule, pw;
+  double* rms;  // non-null: Err / div goes there instead, and nothing is decided
+  double div;
 };
 
 struct EpiParams {
@@ -265,6 +267,8 @@ hipError_t launch_widen(const float* z32, int np, double* z64r, double* z64c, hi
                         float* zc32 = nullptr, u16* prh = nullptr, u16* prl = nullptr,
                         u16* pch = nullptr, u16* pcl = nullptr, float scale = 1.0f,
                         int fmt = PAIR_BF16);
+hipError_t launch_stage_residual(const double* S, const double* Z, int n, int np, double* s64,
+                                 double* zc64, int* clear, hipStream_t st);
 hipError_t launch_unpad_f64(const double* src, int np, int n, double* dst, hipStream_t st);
 hipError_t launch_unpad_f32(const float* src, int np, int n, double* dst, hipStream_t st);
 // out[0] = sqrt(sum of the partials) / div (div = 1: the Frobenius norm itself)
