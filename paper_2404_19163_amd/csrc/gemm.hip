@@ -82,20 +82,42 @@ __global__ void __launch_bounds__(WM* WN * 64)
 // ---------------------------------------------------------------------------
 // FP64 kernel
 // ---------------------------------------------------------------------------
-template <int T, bool SYM>
-__global__ void __launch_bounds__(F64Cfg<T>::NT, 4)
+// The tiles are 64 wide, except those whose row-major number is nbig or more: each of these is
+// four 32-wide ones (f64_whole_tiles), done by the last blocks, as every CU should have its
+// share of the large tiles before the small ones fill in.
+template <bool SYM>
+__global__ void __launch_bounds__(256, 4)
     gemm_f64_kernel(const double* __restrict__ A, int lda, const double* __restrict__ B, int ldb,
-                    int K, int tiles_n, int gm, EpiParams ep) {
-  using C = F64Cfg<T>;
-  __shared__ __attribute__((aligned(16))) double lds[C::LDS];
-  __shared__ double red[C::NT / 64];
+                    int K, int tiles, int nbig, int tiles_n, int gm, EpiParams ep) {
+  using C64 = F64Cfg<64>;
+  using C32 = F64Cfg<32>;
+  static_assert(C64::LDS == C32::LDS && C64::NT == 256 && C32::NT == 256, "one block shape");
+  __shared__ __attribute__((aligned(16))) double lds[C64::LDS];
+  __shared__ double red[4];
   if (ep.gate && *ep.gate) return;
-  const int bid = xcd_remap(blockIdx.x, gridDim.x);
-  int ti, tj;
-  tile_coords(bid, tiles_n, SYM, ti, tj, gm);
-  const int mode = SYM ? (ti == tj ? 2 : 1) : 0;
-  f64_tile<T, T, C::WM, C::WN, C::NS>(A, lda, B, ldb, K, ti * T, tj * T, mode, ep,
-                                      tile_index(ti, tj, tiles_n, SYM), lds, red);
+  const int bid = blockIdx.x;
+  int ti, tj, sub = 0;
+  if (bid < nbig) {  // in bands or groups where they are the whole grid
+    tile_coords(xcd_remap(bid, nbig), tiles_n, SYM, ti, tj, nbig == tiles ? gm : 1);
+  } else {
+    const int j = xcd_remap(bid - nbig, gridDim.x - nbig);
+    tile_coords(nbig + j / 4, tiles_n, SYM, ti, tj, 1);
+    sub = j % 4;
+  }
+  const int t = tile_index(ti, tj, tiles_n, SYM);
+  if (t < nbig) {
+    f64_tile<64, 64, C64::WM, C64::WN, C64::NS>(A, lda, B, ldb, K, ti * 64, tj * 64,
+                                                SYM ? (ti == tj ? 2 : 1) : 0, ep, t, lds, red);
+    return;
+  }
+  const int pidx = nbig + 4 * (t - nbig) + sub;
+  const int si = 2 * ti + (sub >> 1), sj = 2 * tj + (sub & 1);
+  if (SYM && si > sj) {  // below the diagonal: written from its mirror
+    if (ep.partials) block_norm_store<256>(0.0, ep, pidx, red);
+    return;
+  }
+  f64_tile<32, 32, C32::WM, C32::WN, C32::NS>(A, lda, B, ldb, K, si * 32, sj * 32,
+                                              SYM ? (si == sj ? 2 : 1) : 0, ep, pidx, lds, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -154,21 +176,25 @@ int x3_tile_edge(int M, int N, bool sym) {
 int x3_blocks(int M, int N, bool sym) { return grid_blocks(M, N, x3_tile_edge(M, N, sym), sym); }
 
 
-// FP64 tile edge.  A 64-wide tile keeps its CU's matrix cores at 0.9 of their rate, a
-// 32-wide one at 0.7 (twice the operand traffic per flop), but a quarter of the size
-// spreads a small grid over more CUs and ends it in a shorter last round.  So the edge
-// with the lower estimated time of the fullest CU is taken: ceil(tiles / 256) units for 64,
-// 1.2 / 4 of that count's for 32.  Measured, 64- against 32-wide: N = 512 full 19.3 / 7.6 us,
-// N = 1024 full 38.7 / 39.3, symmetric 37.1 / 29.9, N = 2048 full 262 / 331, symmetric
-// 186 / 181, N = 3072 symmetric 519 / 606.  ZF_F64_TILE / ZF_F64_SYM_TILE (32 or 64) force
-// an edge (tuning).
-int f64_tile_edge(int M, int N, bool sym) {
+// FP64 tiles of a launch that stay 64 wide.  A 64-wide tile keeps its CU's matrix cores at 0.9
+// of their rate, a 32-wide one at 0.7 (twice the operand traffic per flop), but a quarter of
+// the size spreads a small number of tiles over more CUs.  So full rounds over the 256 CUs
+// stay whole, and the tiles beyond them are quartered where that gives at most three
+// 32-wide tiles a CU (1.2 / 4 of a 64-wide one's time each), which is up to 192 of them, and
+// where a round weighs enough: from six on, the blocks' own drift evens the rest out.
+// Measured per launch, all 64 / all 32 / this rule, us: full N = 512 23 / 11 / 11, N = 1024
+// 42 / 41 / 41, N = 1536 143 / 122 / 110, N = 2500 514 / 567 / 514; symmetric N = 1024 41 /
+// 35 / 35, N = 1536 100 / 80 / 68, N = 2048 187 / 161 / 144, N = 2500 298 / 300 / 251,
+// N = 3000 528 / 500 / 432, N = 4096 1110 / 1248 / 1110.
+// ZF_F64_TILE / ZF_F64_SYM_TILE force all 64 or all 32 (tuning).
+static int f64_whole_tiles(int M, int N, bool sym) {
+  const int tiles = grid_blocks(M, N, 64, sym);
   const char* env = getenv(sym ? "ZF_F64_SYM_TILE" : "ZF_F64_TILE");
   const int want = env ? atoi(env) : 0;
-  if (want == 32 || want == 64) return want;
-  const int c64 = (grid_blocks(M, N, 64, sym) + 255) / 256;
-  const int c32 = (grid_blocks(M, N, 32, sym) + 255) / 256;
-  return 1.2 * c32 < 4.0 * c64 ? 32 : 64;
+  if (want == 32) return 0;
+  if (want == 64) return tiles;
+  const int rest = tiles % 256;
+  return rest <= 192 && tiles < 6 * 256 ? tiles - rest : tiles;
 }
 
 // Row-group height of the full-grid tile order: 4 (a run of 32 tiles on one XCD then
@@ -190,7 +216,14 @@ static int sym_group() {
   return g >= 1 ? g : 1;
 }
 
-int f64_blocks(int M, int N, bool sym) { return grid_blocks(M, N, f64_tile_edge(M, N, sym), sym); }
+int f64_blocks(int M, int N, bool sym) {
+  const int tiles = grid_blocks(M, N, 64, sym);
+  return tiles + 3 * (tiles - f64_whole_tiles(M, N, sym));
+}
+
+double f64_elements(int M, int N, bool sym) {
+  return 64.0 * 64.0 * grid_blocks(M, N, 64, sym);
+}
 
 int max_blocks(int M, int N) { return grid_blocks(M, N, 32, false); }
 
@@ -217,17 +250,6 @@ static void f32_launch(const float* A, int lda, const float* B, int ldb, int M, 
   else
     hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, WM, WN, false>), dim3(blocks), dim3(WM * WN * 64),
                        0, st, A, lda, B, ldb, K, N / BN, tile_group(M, BM), ep);
-}
-
-template <int T>
-static void f64_launch(const double* A, int lda, const double* B, int ldb, int M, int N, int K,
-                       bool sym, int blocks, const EpiParams& ep, hipStream_t st) {
-  if (sym)
-    hipLaunchKernelGGL((gemm_f64_kernel<T, true>), dim3(blocks), dim3(F64Cfg<T>::NT), 0, st, A,
-                       lda, B, ldb, K, N / T, sym_group(), ep);
-  else
-    hipLaunchKernelGGL((gemm_f64_kernel<T, false>), dim3(blocks), dim3(F64Cfg<T>::NT), 0, st, A,
-                       lda, B, ldb, K, N / T, tile_group(M, T), ep);
 }
 
 template <int PM>
@@ -307,11 +329,14 @@ hipError_t launch_gemm_f32(const float* A, int lda, const float* B, int ldb, int
 hipError_t launch_gemm_f64(const double* A, int lda, const double* B, int ldb, int M, int N, int K,
                            bool sym, const EpiParams& ep, hipStream_t st) {
   if (!dims_ok(M, N, K, sym)) return hipErrorInvalidValue;
-  const int blocks = f64_blocks(M, N, sym);
-  if (f64_tile_edge(M, N, sym) == 32)
-    f64_launch<32>(A, lda, B, ldb, M, N, K, sym, blocks, ep, st);
+  const int tiles = grid_blocks(M, N, 64, sym), whole = f64_whole_tiles(M, N, sym);
+  const dim3 grid(tiles + 3 * (tiles - whole));
+  if (sym)
+    hipLaunchKernelGGL(gemm_f64_kernel<true>, grid, dim3(256), 0, st, A, lda, B, ldb, K, tiles,
+                       whole, N / 64, sym_group(), ep);
   else
-    f64_launch<64>(A, lda, B, ldb, M, N, K, sym, blocks, ep, st);
+    hipLaunchKernelGGL(gemm_f64_kernel<false>, grid, dim3(256), 0, st, A, lda, B, ldb, K, tiles,
+                       whole, N / 64, tile_group(M, 64), ep);
   return hipGetLastError();
 }
 

@@ -453,8 +453,7 @@ static int gemm_f64(const double* A, const double* B, int np, bool sym, const Ep
     pe.a = take_event();
     pe.b = take_event();
     pe.cls = sym ? K_F64_SYM : K_F64;
-    const double t = (double)f64_tile_edge(np, np, sym);
-    pe.flops = 2.0 * (double)f64_blocks(np, np, sym) * t * t * (double)np;
+    pe.flops = 2.0 * f64_elements(np, np, sym) * (double)np;
     HIP_TRY(hipEventRecord(pe.a, st));
   }
   HIP_TRY(launch_gemm_f64(A, np, B, np, np, np, np, sym, ep, st));

@@ -198,7 +198,7 @@ struct EpiParams {
 constexpr int kTile = 128;
 int x3_tile_edge(int M, int N, bool sym);  // tile edge the BF16x3 launch will use
 int x3_blocks(int M, int N, bool sym);   // blocks (= norm partials) of that launch
-int f64_tile_edge(int M, int N, bool sym);
+double f64_elements(int M, int N, bool sym);  // output elements that launch computes
 int f64_blocks(int M, int N, bool sym);
 int max_blocks(int M, int N);            // upper bound of the above (smallest tile edge)
 

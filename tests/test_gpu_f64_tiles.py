@@ -44,6 +44,22 @@ def test_edges_agree(zf, monkeypatch, m, nn, k, sym):
     assert torch.equal(out["32"], out["64"])
 
 
+@pytest.mark.parametrize("m,nn,sym", [(1200, 1200, False), (1500, 1500, True), (1030, 1290, False),
+                                      (2500, 2500, True), (1100, 1100, True)])
+def test_quartered_rest_agrees(zf, monkeypatch, m, nn, sym):
+    """Grids with a rest beyond full rounds over the CUs (quartered or, beyond 192 tiles, not):
+    the same elements, bit for bit, as 64-wide tiles alone, and a norm of each once."""
+    rng = np.random.default_rng(m + nn)
+    A = torch.from_numpy(rng.standard_normal((m, 70))).cuda()
+    B = A if sym else torch.from_numpy(rng.standard_normal((nn, 70))).cuda()
+    C, s = zf.t_gemm("fp64", A, B, sym=sym)
+    monkeypatch.setenv("ZF_F64_TILE", "64")
+    monkeypatch.setenv("ZF_F64_SYM_TILE", "64")
+    C64, s64 = zf.t_gemm("fp64", A, B, sym=sym)
+    assert torch.equal(C, C64)
+    assert s == pytest.approx(s64, rel=1e-12)
+
+
 @pytest.mark.parametrize("n", [1, 63, 64, 65])
 def test_shortest_contraction(zf, n):
     """One and two 64-wide tiles in the batched path: the shortest K the ring runs."""
