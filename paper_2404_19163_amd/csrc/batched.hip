@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(X3G<T>::NT, 2)
     const BMat& M = mats[tk.m];
     if (!op_applies(op, M)) continue;
     const int np = M.np;
-    EpiParams ep;
+    EpiCore ep;
     memset(&ep, 0, sizeof ep);
     ep.beta = 1.0;
     ep.ld = np;
@@ -225,7 +225,7 @@ __global__ void __launch_bounds__(256, 4)
     if (!op_applies(op, M)) continue;
     const int np = M.np;
     constexpr int T = 64;
-    EpiParams ep;
+    EpiCore ep;
     memset(&ep, 0, sizeof ep);
     ep.beta = 1.0;
     ep.ld = np;

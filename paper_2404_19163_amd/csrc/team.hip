@@ -114,7 +114,7 @@ __device__ __forceinline__ void team_leave(Team& t) {
 // stages: a member takes tiles rank, rank + size, ...
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void stage_x3(const Team& t, int np, const u16* ah, const u16* al, const u16* bh,
-                         const u16* bl, bool sym, const EpiParams& ep, u16* lds, double* red) {
+                         const u16* bl, bool sym, const EpiCore& ep, u16* lds, double* red) {
   const int T = np / 64, count = sym ? T * (T + 1) / 2 : T * T;
   for (int k = t.rank; k < count; k += t.size) {
     int ti, tj;
@@ -128,7 +128,7 @@ __device__ __forceinline__ void stage_x3(const Team& t, int np, const u16* ah, c
 
 // FP64 tiles are 32 wide: they are bound by the XCD's matrix cores, and small orders have few.
 __device__ __forceinline__ void stage_f64(const Team& t, int np, const double* a, const double* b, bool sym,
-                         const EpiParams& ep, u16* lds, double* red) {
+                         const EpiCore& ep, u16* lds, double* red) {
   const int T = np / 32, count = sym ? T * (T + 1) / 2 : T * T;
   using C = F64Cfg<32>;
   for (int k = t.rank; k < count; k += t.size) {
@@ -282,7 +282,7 @@ __device__ __forceinline__ void team_solve(Team& t, MatArg m, const TeamCall& ca
     // operands are read when a stage needs them: held across stages, their addresses would
     // take more scalar registers than there are
     asm volatile("" : "+s"(m));
-    EpiParams e;
+    EpiCore e;
     memset(&e, 0, sizeof e);
     e.beta = 1.0;
     e.ld = np;
