@@ -7,7 +7,7 @@
 // transposed, so no kernel ever needs a transposing load.  Z's transposed pair
 // is K-blocked (kb_offset: 32-wide K blocks, each a row-major panel), which the
 // BF16x3 main loop reads through its per-operand K-block stride and which the
-// update's transposed epilogue writes as one contiguous run per strip.
+// update's transposed epilogue writes as one contiguous 2 KB run per 32 x 32 block.
 //
 //   gemm_x3  : (h)(h) + (h)(l) + (l)(h) of Sec. III.B (Eqs. SZn, Xn, Xsq): each
 //              operand is a BF16 hi/lo pair, the three products accumulate into

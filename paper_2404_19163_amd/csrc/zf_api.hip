@@ -6,7 +6,7 @@
 //   phase H: FP64 residual sweeps (Sec. IV.B, Algorithm 3), ratio-stopped in FP64
 //   output:  Z (FP64, unpadded)
 // A sweep is: residual evaluation (GEMM1 A^T = Z^T S, GEMM2 delta = I - Z^T A,
-// both with Frobenius-norm partials) -> one double to the host -> stop test ->
+// the latter with Frobenius-norm partials) -> stop test on the device ->
 // correction Q = sum_{k>=1} c_k delta^k (m - 1 symmetric GEMMs, Horner) ->
 // GEMM4 Z_new = Z + Z Q into the other half of a ping-pong pair.
 //
@@ -184,7 +184,7 @@ struct Workspace {
   u16 *s_hi = nullptr, *s_lo = nullptr;
   // Z's pair row-major (zr) and transposed (zc).  Every pair of the workspace is
   // K-blocked (kb_offset): a K step of a GEMM tile reads one contiguous run, and
-  // the transposed epilogue writes one per strip.
+  // the transposed epilogue writes one per 32 x 32 block.
   u16 *zr_hi[2] = {}, *zr_lo[2] = {}, *zc_hi[2] = {}, *zc_lo[2] = {};
   u16 *at_hi = nullptr, *at_lo = nullptr, *d_hi = nullptr, *d_lo = nullptr;
   u16 *q_hi = nullptr, *q_lo = nullptr, *u_hi = nullptr, *u_lo = nullptr;

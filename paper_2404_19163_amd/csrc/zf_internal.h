@@ -135,7 +135,7 @@ __host__ __device__ inline bool accept_poly(double c[3], double x_lo) {
 // of an (rows x K) operand at kb_offset(r, k, ld), i.e. K cut into blocks of 32
 // and each block stored as a row-major (ld x 32) panel.  One K step of a GEMM
 // tile then reads a contiguous run of 64-byte rows, and a producer that forms 32
-// consecutive k of many rows (a transposed epilogue strip) writes one contiguous
+// consecutive k of many rows (a block of a transposed epilogue) writes one contiguous
 // run instead of 64-byte pieces one ld apart.
 // ---------------------------------------------------------------------------
 __host__ __device__ inline size_t kb_offset(int r, int k, int ld) {
