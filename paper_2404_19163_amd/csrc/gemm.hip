@@ -300,13 +300,16 @@ hipError_t launch_gemm_x3(const u16* Ahi, const u16* Alo, int lda, const u16* Bh
   return hipGetLastError();
 }
 
-// FP32 tile edge: these tiles' main loop needs larger grids than the pairs' (256 from 128
-// tiles, 128 from 192).
+// FP32 tile edge.  Its matrix-core instruction takes twice as long for the same fragments as
+// a BF16 one, so a 64-wide tile is not held back by operand traffic and, four blocks a CU,
+// leaves the least of the chip idle: 64 / 128 / 256 wide full N = 1024 40 / 89 / 275 us,
+// N = 2048 167 / 175 / 543, N = 3072 527 / 614 / 833, N = 5120 2330 / 2804 / 2780; symmetric
+// N = 3072 314 / 470 / 807, N = 4096 702 / 902 / 1067.  Only whole rounds of 256-wide tiles,
+// one per CU, are faster: full N = 4096 1189 / 1499 / 1150 us.
 int f32_tile_edge(int M, int N, bool sym) {
   if (const int want = forced_edge(M, N, sym)) return want;
-  if (M % 256 == 0 && N % 256 == 0 && grid_blocks(M, N, 256, sym) >= 128) return 256;
-  if (M % 128 == 0 && N % 128 == 0 && grid_blocks(M, N, 128, sym) >= 192) return 128;
-  return 64;
+  const bool whole = M % 256 == 0 && N % 256 == 0 && grid_blocks(M, N, 256, sym) % 256 == 0;
+  return whole ? 256 : 64;
 }
 int f32_blocks(int M, int N, bool sym) {
   return grid_blocks(M, N, f32_tile_edge(M, N, sym), sym);

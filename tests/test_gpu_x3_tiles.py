@@ -84,3 +84,20 @@ def test_192_wide_edge_agrees_bitwise(zf, monkeypatch, prec, n, k, sym):
                               kblocked=True)
     assert torch.equal(out["192"][0], out["64"][0])
     assert out["192"][1] == pytest.approx(out["64"][1], rel=1e-12)
+
+
+@pytest.mark.parametrize("n,sym", [(200, False), (200, True), (1500, True), (2048, False)])
+def test_fp32_edges_agree_bitwise(zf, monkeypatch, n, sym):
+    """The FP32 products of an element run in one order on every tile edge, the chosen one
+    included."""
+    rng = np.random.default_rng(n)
+    A = torch.from_numpy(rng.standard_normal((n, 70))).cuda()
+    B = A if sym else torch.from_numpy(rng.standard_normal((n, 70))).cuda()
+    out = [zf.t_gemm("fp32", A, B, sym=sym)]
+    for tile in ("64", "128", "256"):
+        monkeypatch.setenv("ZF_X3_TILE", tile)
+        monkeypatch.setenv("ZF_X3_SYM_TILE", tile)
+        out.append(zf.t_gemm("fp32", A, B, sym=sym))
+    for C, s in out[1:]:
+        assert torch.equal(C, out[0][0])
+        assert s == pytest.approx(out[0][1], rel=1e-12)
