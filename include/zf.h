@@ -163,7 +163,9 @@ int zf_refine_ex(const double* S, const double* Z0, int n, const zf_opts* opts, 
  * zf_refine_batched -- refine count independent matrices of uneven order together.
  *   count       1..65535 matrices.
  *   S[m], Z[m]  device pointers (host arrays of count pointers), n[m] x n[m] FP64, n[m] in
- *               1..8192; Z0 may be NULL (all scaled identity) or hold NULL entries.
+ *               1..8192; Z0 may be NULL (all scaled identity) or hold NULL entries.  A Z[m]
+ *               may alias any S[k] or Z0[k]: no result is written before every input that it
+ *               overlaps has been read.
  *   opts        order must be 2, precision ZF_BF16X3, refine ZF_REFINE_OFF or
  *               ZF_REFINE_F64_DELTA (opts NULL = defaults).  opts.z0 = ZF_Z0_LEARNED
  *               gives every matrix without a Z0 the learned guess (per-matrix
@@ -180,8 +182,9 @@ int zf_refine_ex(const double* S, const double* Z0, int n, const zf_opts* opts, 
  * the table of
  * zf_batched_set_tiles / zf_batched_autotune.  A batch whose orders are all at most 512
  * runs in one kernel instead, each matrix by a team of workgroups of its own, without
- * lockstep (the same iterates; only the rounding of the residual norms differs), unless
- * zf_batched_use_graph(0) asks for eager macro-sweeps.  Returns the OR of the warnings, or
+ * lockstep (the same iterates; only the rounding of the residual norms differs), unless a
+ * Z[m] overlaps another matrix's S or Z0, or zf_batched_use_graph(0) asks for eager
+ * macro-sweeps.  Returns the OR of the warnings, or
  * the first failing matrix's error (every result is still filled).
  */
 int zf_refine_batched(int count, const double* const* S, const double* const* Z0, const int* n,

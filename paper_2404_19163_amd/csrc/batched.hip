@@ -1162,7 +1162,10 @@ static int batched_impl(int count, const double* const* S, const double* const* 
   call.c[1] = 0.5;
   call.c[2] = 0.375;
   call.spin = team_spin_ticks();
-  const bool teams = allow_teams && g_use_graph && max_n <= team_batch_max();
+  // Lockstep reads every S and Z0 before it writes the first Z; a team writes its Z while
+  // others have not started, and a matrix redone after a late team reads its inputs last.
+  const bool teams = allow_teams && g_use_graph && max_n <= team_batch_max() &&
+                     !results_overlap_inputs(count, S, Z0, n, Z);
   // the batch by teams; matrices whose team gave up (their Z is untouched) by macro-sweeps
   auto by_teams = [&](std::vector<BMat>& out) -> int {
     const TeamOut* to = nullptr;

@@ -1,12 +1,13 @@
 // Index arithmetic shared by the device kernels and the host planners: the order in
 // which a GEMM grid walks its output tiles, the norm-partial slot of a tile, the
 // renumbering of blocks over the 8 XCDs, the task tables of the grouped (batched)
-// GEMMs and the 3 x 3 solve of the learned guess's labels.  Everything here is plain
-// integer / FP64 arithmetic, so the header also builds for the host alone, where a
+// GEMMs, the overlap of a batch's results with its inputs and the 3 x 3 solve of the learned
+// guess's labels.  Everything here is plain integer / FP64 arithmetic, so the header also builds for the host alone, where a
 // sanitizer test exercises it.
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stdint.h>
 
 #include <algorithm>
 #include <cmath>
@@ -125,6 +126,55 @@ inline void build_task_tables(int count, const int* np, const int* tile,
   }
   fseg[16] = (int)full.size();
   sseg[16] = (int)sym.size();
+}
+
+// ---------------------------------------------------------------------------
+// results of a batch that are other matrices' inputs
+// ---------------------------------------------------------------------------
+// Whether the result Z[m] of some matrix overlaps S[k] or Z0[k] of another one (Z0 or an entry
+// of it may be null; all n[m] x n[m] doubles).  The results are sorted by their first byte;
+// of those that begin before an input ends, one that ends behind the input's start overlaps
+// it, so the furthest end and the furthest of another matrix decide.
+inline bool results_overlap_inputs(int count, const double* const* S, const double* const* Z0,
+                                   const int* n, const double* const* Z) {
+  struct Out {
+    uintptr_t begin, end;
+    int m;
+    uintptr_t top, other;  // furthest end so far, and the furthest of another matrix than top_m
+    int top_m;
+  };
+  auto bytes = [&](int m) { return sizeof(double) * (uintptr_t)n[m] * (uintptr_t)n[m]; };
+  std::vector<Out> out(count);
+  for (int m = 0; m < count; ++m) {
+    const uintptr_t b = reinterpret_cast<uintptr_t>(Z[m]);
+    out[m] = Out{b, b + bytes(m), m, 0, 0, -1};
+  }
+  std::sort(out.begin(), out.end(), [](const Out& a, const Out& b) { return a.begin < b.begin; });
+  uintptr_t top = 0, other = 0;
+  int top_m = -1;
+  for (Out& o : out) {
+    if (o.end > top) {
+      other = top;
+      top = o.end;
+      top_m = o.m;
+    } else if (o.end > other) {
+      other = o.end;
+    }
+    o.top = top;
+    o.other = other;
+    o.top_m = top_m;
+  }
+  auto hit = [&](const double* p, int k) {
+    const uintptr_t b = reinterpret_cast<uintptr_t>(p), e = b + bytes(k);
+    auto it = std::lower_bound(out.begin(), out.end(), e,
+                               [](const Out& o, uintptr_t v) { return o.begin < v; });
+    if (it == out.begin()) return false;
+    --it;
+    return (it->top_m == k ? it->other : it->top) > b;
+  };
+  for (int k = 0; k < count; ++k)
+    if (hit(S[k], k) || (Z0 && Z0[k] && hit(Z0[k], k))) return true;
+  return false;
 }
 
 // ---------------------------------------------------------------------------
