@@ -681,9 +681,10 @@ struct BatchState {
   hipGraphExec_t exec = nullptr;
   std::vector<char> key;  // layout the captured graph was built for
   // teams: records, report and histories on the device, the same in pinned memory, and the
-  // meeting points (zero between launches)
+  // meeting points, zero between launches (not known to be: team_ready false)
   void *team = nullptr, *team_host = nullptr, *team_ctl = nullptr;
-  size_t team_bytes = 0, team_host_bytes = 0, team_ctls = 0;
+  size_t team_bytes = 0, team_host_bytes = 0, team_ctl_bytes = 0;
+  bool team_ready = false;
 };
 static BatchState g_b;
 
@@ -945,16 +946,9 @@ static int run_teams(const std::vector<BMat>& mats, double* partials, const doub
   if (rc < 0) return rc;
   rc = grow_pinned(&g_b.team_host, &g_b.team_host_bytes, total);
   if (rc < 0) return rc;
-  if (g_b.team_ctls < (size_t)count) {
-    size_t have = 0;
-    if (g_b.team_ctl) (void)hipFree(g_b.team_ctl);
-    g_b.team_ctl = nullptr;
-    g_b.team_ctls = 0;
-    rc = grow(&g_b.team_ctl, &have, sizeof(TeamCtl) * count);
-    if (rc < 0) return rc;
-    BHIP_TRY(hipMemset(g_b.team_ctl, 0, sizeof(TeamCtl) * count));
-    g_b.team_ctls = count;
-  }
+  if (g_b.team_ctl_bytes < sizeof(TeamCtl) * count) g_b.team_ready = false;
+  rc = grow(&g_b.team_ctl, &g_b.team_ctl_bytes, sizeof(TeamCtl) * count);
+  if (rc < 0) return rc;
   char* d = (char*)g_b.team;
   char* h = (char*)g_b.team_host;
   TeamMat* tm = (TeamMat*)h;
@@ -993,11 +987,15 @@ static int run_teams(const std::vector<BMat>& mats, double* partials, const doub
     t.ctl = (TeamCtl*)g_b.team_ctl + m;
   }
   memcpy(h + o_slots, slots.data(), sizeof(TeamSlot) * slots.size());
+  // cleared on the stream of the launch that reads them; again after a call that failed
+  if (!g_b.team_ready) BHIP_TRY(launch_fill_zero(g_b.team_ctl, g_b.team_ctl_bytes, st));
+  g_b.team_ready = false;
   BHIP_TRY(hipMemcpyAsync(d, h, up, hipMemcpyHostToDevice, st));
   BHIP_TRY(launch_team_many((const TeamMat*)d, (const TeamSlot*)(d + o_slots), (int)slots.size(),
                             call, st));
   BHIP_TRY(hipMemcpyAsync(h + up, d + up, total - up, hipMemcpyDeviceToHost, st));
   BHIP_TRY(hipStreamSynchronize(st));
+  g_b.team_ready = true;
   *outs = (const TeamOut*)(h + up);
   *hists = (const double*)(h + o_hist);
   return 0;

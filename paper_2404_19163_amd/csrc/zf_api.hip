@@ -210,15 +210,16 @@ struct Workspace {
   double *gscr = nullptr, *cg = nullptr;  // learned-guess scratch (8192) and coefficients (8)
   float* feats = nullptr;
   // device-side stop test: each phase's gate (nonzero once it stopped; [0] and [1]) and the
-  // count of finished blocks ([2]), the previous Err, and a ring of kBoxSlots words the host
+  // count of finished blocks ([2]), all cleared by the first launch of a call, the previous Err, and a ring of kBoxSlots words the host
   // reads (pinned, coherent, written by the device; box_dev is its device address;
   // kBoxEmpty until then)
   int* gate = nullptr;
   double* prev_dev = nullptr;
   double *box = nullptr, *box_dev = nullptr;
-  // one-kernel refinement of small orders (team.hip): its meeting point, and its report
-  // and residual history in pinned memory
+  // one-kernel refinement of small orders (team.hip): its meeting point, whether that is
+  // known to be zero, and its report and residual history in pinned memory
   TeamCtl* team_ctl = nullptr;
+  bool team_ready = false;
   TeamReport *team = nullptr, *team_dev = nullptr;
 };
 constexpr int kBoxSlots = 8;
@@ -274,8 +275,6 @@ static int ws_build(Workspace& w, int dev, int np, bool x3, bool f64, bool f32, 
   ZF_TRY(ws_alloc(w, &w.cg, 8));
   ZF_TRY(ws_alloc(w, &w.feats, 64));
   ZF_TRY(ws_alloc(w, &w.gate, kGateWords));
-  if (hipMemset(w.gate, 0, kGateWords * sizeof(int)) != hipSuccess)
-    return fail(ZF_ERR_HIP, "hipMemset of the gates failed");
   ZF_TRY(ws_alloc(w, &w.prev_dev, 1));
   if (hipHostMalloc((void**)&w.box, kBoxSlots * sizeof(double),
                     hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
@@ -284,8 +283,7 @@ static int ws_build(Workspace& w, int dev, int np, bool x3, bool f64, bool f32, 
     return fail(ZF_ERR_NOMEM, "hipHostMalloc of the stop-test mailbox failed");
   }
   ZF_TRY(ws_alloc(w, &w.team_ctl, 1));
-  if (hipMemset(w.team_ctl, 0, sizeof(TeamCtl)) != hipSuccess ||
-      hipHostMalloc((void**)&w.team, sizeof(TeamReport),
+  if (hipHostMalloc((void**)&w.team, sizeof(TeamReport),
                     hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
       hipHostGetDevicePointer((void**)&w.team_dev, w.team, 0) != hipSuccess) {
     (void)hipGetLastError();
@@ -1027,8 +1025,13 @@ static int team_refine(Workspace& w, const double* S, const double* Z0, int n, b
   // with 32 members, 293 with 64; mixed 244 and 266).
   const int T = m.np / (fp64 || refine ? 32 : 64);
   w.team->out.done = 0;
+  // cleared on the stream of the launch that reads it, as no other stream need be ordered
+  // before that one; again after a call that failed
+  if (!w.team_ready) HIP_TRY(launch_fill_zero(w.team_ctl, sizeof(TeamCtl), st));
+  w.team_ready = false;
   HIP_TRY(launch_team_one(m, call, std::min(T * T, fp64 ? kTeamMaxSize : 32), st));
   HIP_TRY(hipStreamSynchronize(st));
+  w.team_ready = true;
   return w.team->out.done ? 1 : 0;
 }
 
