@@ -299,7 +299,7 @@ __global__ void decide_kernel(BMat* mats, int count, const double* __restrict__ 
     }
     const int it = M.it;
     bool stop = false;
-    if (it > 0) stop = (rule == ZF_STOP_MONOTONE) ? (err >= M.prev) : (err > pow(M.prev, (double)(order + 1)));
+    if (it > 0) stop = (rule == ZF_STOP_MONOTONE) ? (err >= M.prev) : above_power(err, M.prev, order + 1);
     const int cap = (M.phase == PH_LOW) ? max_l : max_h;
     bool finish = false;
     int upd = it;

@@ -149,16 +149,6 @@ __device__ __forceinline__ double team_norm(const double* partials, int count) {
   return sqrt(wave_sum(s));
 }
 
-// err > prev^pw as pow() would have it; pow() itself is only called when the power is too
-// close to err for its error bound.
-__device__ __forceinline__ bool above_power(double err, double prev, int pw) {
-  double p = prev;
-  for (int k = 1; k < pw; ++k) p *= prev;
-  if (err > p * (1.0 + 1e-14)) return true;
-  if (err < p * (1.0 - 1e-14)) return false;
-  return err > pow(prev, (double)pw);
-}
-
 // FP32 master -> FP64 row-major and transposed, 64 x 64 tiles through LDS.
 __device__ __forceinline__ void team_widen(const Team& t, MatArg m, int cur, u16* lds) {
   float* tv = reinterpret_cast<float*>(lds);  // 64 x 65

@@ -1,9 +1,9 @@
 // Index arithmetic shared by the device kernels and the host planners: the order in
 // which a GEMM grid walks its output tiles, the norm-partial slot of a tile, the
 // renumbering of blocks over the 8 XCDs, the task tables of the grouped (batched)
-// GEMMs, the overlap of a batch's results with its inputs and the 3 x 3 solve of the learned
-// guess's labels.  Everything here is plain integer / FP64 arithmetic, so the header also builds for the host alone, where a
-// sanitizer test exercises it.
+// GEMMs, the ratio stop rule, the overlap of a batch's results with its inputs and the 3 x 3
+// solve of the learned guess's labels.  Everything here is plain integer / FP64 arithmetic, so
+// the header also builds for the host alone, where a sanitizer test exercises it.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -126,6 +126,21 @@ inline void build_task_tables(int count, const int* np, const int* tile,
   }
   fseg[16] = (int)full.size();
   sseg[16] = (int)sym.size();
+}
+
+// ---------------------------------------------------------------------------
+// the ratio stop rule
+// ---------------------------------------------------------------------------
+// err > pow(prev, pw), which every path stops by.  pow() itself is only called where the power
+// is too close to err, or to the smallest numbers, for the error bound of the product.
+__host__ __device__ inline bool above_power(double err, double prev, int pw) {
+  double p = prev;
+  for (int k = 1; k < pw; ++k) p *= prev;
+  if (p > 1e-280) {
+    if (err > p * (1.0 + 1e-14)) return true;
+    if (err < p * (1.0 - 1e-14)) return false;
+  }
+  return err > pow(prev, (double)pw);
 }
 
 // ---------------------------------------------------------------------------

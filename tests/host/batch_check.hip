@@ -1,6 +1,7 @@
-// Host-only check of the batched path's host arithmetic (zf_index.h), built and run by
-// tests/test_host_batch.py under AddressSanitizer and UBSan.  Prints "ok <checks>" or the
+// Host-only check of the batched path's host arithmetic and of the ratio stop rule
+// (zf_index.h), built and run by tests/test_host_batch.py under AddressSanitizer and UBSan.  Prints "ok <checks>" or the
 // first failure and exits non-zero.
+#include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -58,8 +59,34 @@ static void overlaps(std::mt19937& rng) {
   CHECK(hits > 2000 && hits < 18000, "%d of 20000 cases overlap", hits);
 }
 
+// above_power is err > pow(prev, pw), also one rounding away from equality, where the power
+// multiplied out gives other answers
+static void powers(std::mt19937& rng) {
+  std::uniform_real_distribution<double> lg(-18.0, 3.0);
+  int differ = 0;
+  for (int t = 0; t < 20000; ++t) {
+    const int pw = 2 + (int)(rng() % 5);
+    const double prev = pow(10.0, lg(rng)), p = pow(prev, (double)pw);
+    double prod = prev;
+    for (int k = 1; k < pw; ++k) prod *= prev;
+    const double near[] = {p, nextafter(p, 0.0), nextafter(p, INFINITY), prod, p * (1.0 + 1e-13),
+                           p * (1.0 - 1e-13), p * 2.0, p * 0.5, prev, 0.0};
+    for (double err : near) {
+      CHECK(above_power(err, prev, pw) == (err > p), "err %.17g prev %.17g pw %d", err, prev, pw);
+      differ += (err > prod) != (err > p);
+    }
+  }
+  CHECK(differ > 100, "%d answers differ from the multiplied power's", differ);
+  for (double prev : {0.0, 1.0, 1e-70, 1e-110, 1e-160, 1e-200, 1e90, 1e160})
+    for (double err : {0.0, 5e-324, 1e-310, 1e-300, 1e-9, 1.0, 1e300})
+      for (int pw = 2; pw <= 6; ++pw)
+        CHECK(above_power(err, prev, pw) == (err > pow(prev, (double)pw)), "err %g prev %g pw %d",
+              err, prev, pw);
+}
+
 int main() {
   std::mt19937 rng(7);
+  powers(rng);
   overlaps(rng);
   printf("ok %ld\n", g_checks);
   return 0;

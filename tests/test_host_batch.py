@@ -1,4 +1,4 @@
-"""Host-only checks of the batched path's host arithmetic under AddressSanitizer and UBSan:
+"""Host-only checks under AddressSanitizer and UBSan: the ratio stop rule (against pow()) and
 which batches have results that are other matrices' inputs (against every pair of ranges).
 Compiled for the host only (hipcc --offload-host-only), so no GPU is needed."""
 import os
