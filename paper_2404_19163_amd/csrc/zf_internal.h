@@ -149,9 +149,9 @@ __host__ __device__ inline size_t kb_offset(int r, int k, int ld) {
 // [row * ld + col]; transposed outputs at [col * ld + row].  With kb set, every
 // 16-bit pair read or written (dhi/dlo, ohi/olo, othi/otlo) is K-blocked instead:
 // (row, col) at kb_offset(row, col, ld), the transposed one at kb_offset(col, row,
-// ld); FP32 and FP64 matrices stay row-major.  In symmetric mode the caller passes
-// the same matrices for both, and the kernel writes the upper triangle normally
-// and mirrors it.
+// ld); FP32 and FP64 matrices stay row-major.  In symmetric mode D is
+// symmetric, the caller passes the same matrices for both, and the kernel writes the
+// upper triangle normally and mirrors it.
 // ---------------------------------------------------------------------------
 // The stop test of one sweep, run by the block of the residual product that finishes last:
 // Err from the norm partials, then the rule of Algorithm 2 against the previous Err
