@@ -685,6 +685,7 @@ struct BatchState {
   void *team = nullptr, *team_host = nullptr, *team_ctl = nullptr;
   size_t team_bytes = 0, team_host_bytes = 0, team_ctl_bytes = 0;
   bool team_ready = false;
+  TeamRest team_rest;
 };
 static BatchState g_b;
 
@@ -1159,11 +1160,11 @@ static int batched_impl(int count, const double* const* S, const double* const* 
   call.c[0] = 1.0;
   call.c[1] = 0.5;
   call.c[2] = 0.375;
-  call.spin = team_spin_ticks();
+  call.spin = team_spin_ticks(true);
   // Lockstep reads every S and Z0 before it writes the first Z; a team writes its Z while
   // others have not started, and a matrix redone after a late team reads its inputs last.
   const bool teams = allow_teams && g_use_graph && max_n <= team_batch_max() &&
-                     !results_overlap_inputs(count, S, Z0, n, Z);
+                     !results_overlap_inputs(count, S, Z0, n, Z) && g_b.team_rest.team();
   // the batch by teams; matrices whose team gave up (their Z is untouched) by macro-sweeps
   auto by_teams = [&](std::vector<BMat>& out) -> int {
     const TeamOut* to = nullptr;
@@ -1194,6 +1195,7 @@ static int batched_impl(int count, const double* const* S, const double* const* 
     std::vector<zf_result> r2(redo.size());
     std::vector<double> h2(redo.size() * (size_t)hist_cap);
     if (!redo.empty()) {
+      g_b.team_rest.late(team_rest_calls());
       const std::vector<double> hs(th, th + (size_t)count * hcap);  // the call below reuses it
       std::vector<const double*> s2, z2;
       std::vector<double*> o2;

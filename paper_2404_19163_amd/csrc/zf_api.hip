@@ -220,6 +220,7 @@ struct Workspace {
   // known to be zero, and its report and residual history in pinned memory
   TeamCtl* team_ctl = nullptr;
   bool team_ready = false;
+  TeamRest team_rest;
   TeamReport *team = nullptr, *team_dev = nullptr;
 };
 constexpr int kBoxSlots = 8;
@@ -961,10 +962,21 @@ static int team_max_order(bool fp64) {
   return fp64 ? 256 : 320;
 }
 
-// Longest wait of a team for its members: 0.2 s (ZF_TEAM_SPIN, in 10 ns ticks, for tests).
-long long team_spin_ticks() {
+// Longest wait of a team for its members.  A meeting takes 1 us and a solve 0.1 to 0.4 ms, so
+// 2 ms are out of the ordinary; in a batch, where a team's last members queue behind earlier
+// teams (1 ms each, some 10 ms at the sweep caps), 20 ms.  ZF_TEAM_SPIN, in 10 ns ticks, for
+// tests.
+long long team_spin_ticks(bool batch) {
   const char* env = getenv("ZF_TEAM_SPIN");
-  return env ? atoll(env) : 20000000ll;
+  return env ? atoll(env) : batch ? 2000000ll : 200000ll;
+}
+
+// 32 calls: a wait in vain then costs 0.06 ms a call while the XCD stays held.  ZF_TEAM_REST
+// overrides; none where ZF_TEAM_SPIN makes teams late.
+int team_rest_calls() {
+  const char* env = getenv("ZF_TEAM_REST");
+  if (env) return std::max(atoi(env), 0);
+  return getenv("ZF_TEAM_SPIN") ? 0 : 32;
 }
 
 // The whole solve by one team.  Returns 1 when it is done (the report is in w.team), 0 when the
@@ -1019,7 +1031,7 @@ static int team_refine(Workspace& w, const double* S, const double* Z0, int n, b
   call.refine = refine;
   call.setup = 1;
   series(o.order, call.c);
-  call.spin = team_spin_ticks();
+  call.spin = team_spin_ticks(false);
   // A member per 64-wide tile; where FP64 products run too, per 32-wide tile of theirs.  Past
   // 32 members two share a CU, which only the all-FP64 recursion gains from (N = 256: 330 us
   // with 32 members, 293 with 64; mixed 244 and 266).
@@ -1032,6 +1044,7 @@ static int team_refine(Workspace& w, const double* S, const double* Z0, int n, b
   HIP_TRY(launch_team_one(m, call, std::min(T * T, fp64 ? kTeamMaxSize : 32), st));
   HIP_TRY(hipStreamSynchronize(st));
   w.team_ready = true;
+  if (!w.team->out.done) w.team_rest.late(team_rest_calls());
   return w.team->out.done ? 1 : 0;
 }
 
@@ -1101,7 +1114,7 @@ static int refine_core(const double* S, const double* Z0, int n, const zf_opts& 
   const bool team = (la == AR_X3 || la == AR_F64) && !learned && !log && !g_prof.on &&
                     (!refine || o.refine == ZF_REFINE_F64_DELTA) && n <= team_max_order(fp64_only) &&
                     max_l < kTeamHist / 2 && max_h < kTeamHist / 2 - 2;
-  if (team) {
+  if (team && w->team_rest.team()) {
     const int tr = team_refine(*w, S, Z0, n, fp64_only, refine, o, max_l, max_h, Z, st);
     if (tr < 0) return tr;
     if (tr == 1) {

@@ -51,7 +51,18 @@ struct TeamCall {
   long long spin;  // longest wait for a team, in ticks of the 100 MHz clock
 };
 
-long long team_spin_ticks();  // TeamCall::spin of a call (zf_api.hip)
+// A late team says that its XCD is held, as a rule by other processes' teams that wait for
+// members too.  The next calls then go by launches at once instead of waiting in vain.
+struct TeamRest {
+  int calls = 0;  // calls still to go by launches
+  bool team() { return calls == 0 || calls-- == 0; }  // whether the next call is for a team
+  void late(int rest) { calls = rest; }
+};
+
+// zf_api.hip: TeamCall::spin of a call (a batch's teams also wait for the teams ahead of them),
+// and the calls that go by launches after a late team.
+long long team_spin_ticks(bool batch);
+int team_rest_calls();
 
 // One matrix, its team on one XCD.
 hipError_t launch_team_one(const TeamMat& m, const TeamCall& call, int size, hipStream_t st);

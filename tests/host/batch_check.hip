@@ -1,5 +1,5 @@
 // Host-only check of the batched path's host arithmetic and of the ratio stop rule
-// (zf_index.h), built and run by tests/test_host_batch.py under AddressSanitizer and UBSan.  Prints "ok <checks>" or the
+// (zf_index.h) and of the calls after a late team (zf_team.h), built and run by tests/test_host_batch.py under AddressSanitizer and UBSan.  Prints "ok <checks>" or the
 // first failure and exits non-zero.
 #include <math.h>
 #include <stdio.h>
@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "zf_index.h"
+#include "zf_team.h"
 
 using namespace zf;
 
@@ -84,7 +85,21 @@ static void powers(std::mt19937& rng) {
               err, prev, pw);
 }
 
+// after a late team the given number of calls go by launches, then a team is tried again
+static void rests() {
+  for (int rest : {0, 1, 3, 32}) {
+    TeamRest r;
+    for (int k = 0; k < 5; ++k) CHECK(r.team(), "a rest without a late team");
+    for (int again = 0; again < 2; ++again) {
+      r.late(rest);
+      for (int k = 0; k < rest; ++k) CHECK(!r.team(), "rest %d ended after %d calls", rest, k);
+      for (int k = 0; k < 5; ++k) CHECK(r.team(), "rest %d goes on", rest);
+    }
+  }
+}
+
 int main() {
+  rests();
   std::mt19937 rng(7);
   powers(rng);
   overlaps(rng);

@@ -64,3 +64,27 @@ def test_results_over_inputs(zf):
     assert _by_teams(zf)
     for a, b in zip(want, s):
         assert torch.equal(a, b)
+
+
+def test_calls_after_a_late_team(zf, monkeypatch):
+    """After a late team the next calls go by launches, then teams are tried again; the
+    factors are the same throughout, in batches and in single solves."""
+    S = [_overlap(n, n) for n in (129, 200, 256)]
+    want = [r.Z.clone() for r in zf.refine_batched(S).results]
+    assert _by_teams(zf)
+    single = zf.refine(S[2])
+    monkeypatch.setenv("ZF_TEAM_REST", "3")
+    monkeypatch.setenv("ZF_TEAM_SPIN", "0")
+    late = [zf.refine_batched(S), zf.refine(S[2])]
+    monkeypatch.delenv("ZF_TEAM_SPIN")
+    teams = []
+    for _ in range(5):
+        r = zf.refine_batched(S)
+        teams.append(_by_teams(zf))
+        late += [r, zf.refine(S[2])]
+    assert teams == [False, False, False, True, True]
+    for r in late:
+        if isinstance(r, zf.Refined):
+            assert torch.equal(r.Z, single.Z) and r.iters == single.iters
+        else:
+            assert all(torch.equal(a.Z, b) for a, b in zip(r.results, want))

@@ -1,5 +1,6 @@
-"""Host-only checks under AddressSanitizer and UBSan: the ratio stop rule (against pow()) and
-which batches have results that are other matrices' inputs (against every pair of ranges).
+"""Host-only checks under AddressSanitizer and UBSan: the ratio stop rule (against pow()),
+which batches have results that are other matrices' inputs (against every pair of ranges),
+and how many calls go without a team after a late one.
 Compiled for the host only (hipcc --offload-host-only), so no GPU is needed."""
 import os
 import shutil
