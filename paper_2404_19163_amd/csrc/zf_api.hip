@@ -784,6 +784,13 @@ struct PhaseOut {
   bool capped = false;
 };
 
+static const char* const kArithName[8] = {"BF16x3", "BF16", "FP32",          "FP64",
+                                          "FP16x3", "FP16", "emulated FP64", "residue-emulated FP64"};
+
+static int fail_nonfinite(Arith da, int it) {
+  return fail(ZF_ERR_NONFINITE, "residual norm is not finite at %s sweep %d", kArithName[da], it);
+}
+
 // One phase of Algorithm 2: evaluate, stop test, update, ping-pong.  The stop test
 // runs on the device (StopTest) and the host queues one sweep ahead: the
 // update of sweep it and the evaluation of sweep it + 1 are launched before the host
@@ -794,8 +801,6 @@ struct PhaseOut {
 // delta's split), so that phase reads each decision before it goes on.
 static int run_phase(Ctx& c, Arith da, Arith ca, bool high, int stop_rule, int max_updates,
                      int& cur, std::vector<double>& hist, PhaseOut& out) {
-  static const char* kName[8] = {"BF16x3", "BF16", "FP32",          "FP64",
-                                 "FP16x3", "FP16", "emulated FP64", "residue-emulated FP64"};
   TraceRange phase_range(high ? "zf.phase_high" : "zf.phase_low");
   Workspace& w = *c.w;
   const bool ahead = !ar_f16(da);
@@ -826,12 +831,12 @@ static int run_phase(Ctx& c, Arith da, Arith ca, bool high, int stop_rule, int m
     if (c.log)
       log_line("\"event\": \"eval\", \"n\": %d, \"arith\": \"%s\", \"phase\": \"%s\", \"it\": %d, "
                "\"err_f\": %.17g, \"rms\": %.6e, \"stop\": %s",
-               c.n, kName[eval_arith(it)], high ? "high" : "low", it, err, err / sqrt((double)c.n),
+               c.n, kArithName[eval_arith(it)], high ? "high" : "low", it, err, err / sqrt((double)c.n),
                code == 1 ? "true" : "false");
     if (code != 0)  // the launches queued ahead were gated off
       for (size_t k = spec; k < g_prof.pending.size(); ++k) g_prof.pending[k].skip = true;
     if (code == 2)
-      return fail(ZF_ERR_NONFINITE, "residual norm is not finite at %s sweep %d", kName[da], it);
+      return fail_nonfinite(da, it);
     if (code == 1) {
       if (err > prev) {  // the previous iterate is still in the other buffer
         cur ^= 1;
@@ -1128,7 +1133,7 @@ static int refine_core(const double* S, const double* Z0, int n, const zf_opts& 
       ph.err = t.err_h;
       flags = t.flags;
       if (t.status == ZF_ERR_NONFINITE)
-        rc = fail(ZF_ERR_NONFINITE, "residual norm is not finite at sweep %d", t.hist_len - 1);
+        rc = t.evals_h > 0 ? fail_nonfinite(AR_F64, t.evals_h - 1) : fail_nonfinite(la, t.evals_l - 1);
       return refine_report(n, fp64_only || refine, h, pl, ph, flags, rc, z0_used, res, hist, hist_cap);
     }
   }

@@ -37,3 +37,19 @@ def test_history_of_an_overflow(zf, n):
     out = zf.refine_batched([S], [Z0], raise_on_error=False)
     assert out.rc == zf.ERR_NONFINITE
     assert out.results[0].hist == [math.inf]
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(refine="off"), dict(precision="fp64", refine="off")])
+def test_message_of_a_failed_solve(zf, monkeypatch, kw):
+    """The one-kernel solve names the arithmetic and the sweep as separate launches do."""
+    S = torch.eye(90, dtype=torch.float64, device="cuda")
+    S[4, 7] = S[7, 4] = float("nan")
+    said = []
+    for limit in ("0", "320"):
+        monkeypatch.setenv("ZF_TEAM_MAX", limit)
+        with pytest.raises(zf.ZFError) as e:
+            zf.refine(S, **kw)
+        assert e.value.code == zf.ERR_NONFINITE
+        said.append(str(e.value))
+    assert said[0] == said[1]
+    assert ("FP64" if "precision" in kw else "BF16x3") + " sweep 0" in said[0]
