@@ -741,15 +741,16 @@ static void build_tables(const std::vector<BMat>& mats, std::vector<TileTask>& f
   build_task_tables((int)mats.size(), np.data(), tile.data(), full, sym, fseg, sseg);
 }
 
-// Buffer sizes for every matrix and the task tables.
-static void make_plan(int count, const int* n, bool with64, Plan& P) {
+// Buffer sizes for every matrix and the task tables.  The tile table is for lockstep: a team's
+// tiles need a multiple of 64 only, and so do the learned guess's launches ahead of teams.
+static void make_plan(int count, const int* n, bool with64, bool teams, Plan& P) {
   P.mats.resize(count);
   size_t bytes = 0;
   for (int m = 0; m < count; ++m) {
     BMat& M = P.mats[m];
     memset(&M, 0, sizeof M);
     M.n = n[m];
-    M.tile = tile_for(n[m]);
+    M.tile = teams ? 64 : tile_for(n[m]);
     M.np = rup(n[m], M.tile);
     const int T = M.np / M.tile;
     M.tiles_sym = T * (T + 1) / 2;
@@ -1095,8 +1096,15 @@ static int batched_impl(int count, const double* const* S, const double* const* 
   if (!g_b.cap) BHIP_TRY(hipStreamCreateWithFlags(&g_b.cap, hipStreamNonBlocking));
   if (!g_b.pinned) BHIP_TRY(hipHostMalloc((void**)&g_b.pinned, 64, hipHostMallocDefault));
 
+  int max_n = 1;
+  for (int m = 0; m < count; ++m) max_n = std::max(max_n, n[m]);
+  // Lockstep reads every S and Z0 before it writes the first Z; a team writes its Z while
+  // others have not started, and a matrix redone after a late team reads its inputs last.
+  const bool teams = allow_teams && g_use_graph && max_n <= team_batch_max() &&
+                     !results_overlap_inputs(count, S, Z0, n, Z) && g_b.team_rest.team();
+
   Plan P;
-  make_plan(count, n, with64, P);
+  make_plan(count, n, with64, teams, P);
   // guesses: given where Z0[m] is set, else learned (opts.z0 = ZF_Z0_LEARNED, network loaded; the
   // device may still fall back) or the scaled identity
   const bool have_net = net_ready();
@@ -1133,8 +1141,6 @@ static int batched_impl(int count, const double* const* S, const double* const* 
   size_t o_stats = align256(o_rem + 64);
   size_t o_coef = align256(o_stats + 32 * (size_t)count);
   size_t o_feat = align256(o_coef + 32 * (size_t)count);
-  int max_n = 1;
-  for (int m = 0; m < count; ++m) max_n = std::max(max_n, n[m]);
   const int stat_chunks = (max_n + kStatRows - 1) / kStatRows;
   size_t o_spart = align256(o_feat + 32 * (size_t)count);
   size_t o_fseg = align256(o_spart + 56 * (size_t)count * stat_chunks);
@@ -1161,10 +1167,6 @@ static int batched_impl(int count, const double* const* S, const double* const* 
   call.c[1] = 0.5;
   call.c[2] = 0.375;
   call.spin = team_spin_ticks(true);
-  // Lockstep reads every S and Z0 before it writes the first Z; a team writes its Z while
-  // others have not started, and a matrix redone after a late team reads its inputs last.
-  const bool teams = allow_teams && g_use_graph && max_n <= team_batch_max() &&
-                     !results_overlap_inputs(count, S, Z0, n, Z) && g_b.team_rest.team();
   // the batch by teams; matrices whose team gave up (their Z is untouched) by macro-sweeps
   auto by_teams = [&](std::vector<BMat>& out) -> int {
     const TeamOut* to = nullptr;

@@ -88,3 +88,28 @@ def test_calls_after_a_late_team(zf, monkeypatch):
             assert torch.equal(r.Z, single.Z) and r.iters == single.iters
         else:
             assert all(torch.equal(a.Z, b) for a, b in zip(r.results, want))
+
+
+@pytest.mark.parametrize("guess", ["identity", "learned"])
+def test_tile_table_is_for_lockstep(zf, monkeypatch, guess):
+    """Teams do not use the table: equal bits, norms included, whatever it says, also where
+    the order is just past a multiple of 64.  In lockstep every edge runs, and agrees in Z."""
+    zf.mlp_set_params([0.0] * zf.N_PARAMS)
+    zf.mlp_set_norm([0.0] * 8, [1.0] * 8, [2.2, -2.0, 0.9], [1.0] * 3)
+    S = [_overlap(n, n) for n in (1, 63, 65, 128, 129, 257, 300, 385, 512)]
+    saved = zf.batched_get_tiles()
+    runs = {}
+    try:
+        for limit in ("512", "0"):
+            monkeypatch.setenv("ZF_TEAM_BATCH_MAX", limit)
+            for edge in (64, 128):
+                zf.batched_set_tiles([1 << 20], [edge])
+                runs[limit, edge] = zf.refine_batched(S, guess=guess).results
+                assert _by_teams(zf) == (limit == "512")
+    finally:
+        zf.batched_set_tiles(*saved)
+    for a, b in zip(runs["512", 64], runs["512", 128]):
+        assert a.hist == b.hist
+    for r in runs.values():
+        for a, b in zip(runs["512", 64], r):
+            assert torch.equal(a.Z, b.Z) and a.iters == b.iters
