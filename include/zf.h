@@ -180,10 +180,10 @@ int zf_refine_ex(const double* S, const double* Z0, int n, const zf_opts* opts, 
  * launches it and reads the live count once per launch, and kernels of macro-sweeps
  * after every matrix has stopped return at once.  The tile edge per matrix comes from
  * the table of zf_batched_set_tiles / zf_batched_autotune.  A batch whose orders are all at
- * most 512 runs in one kernel instead, each matrix by a team of workgroups of its own,
- * without lockstep and without the table (the same iterates; only the rounding of the
- * residual norms differs), unless a Z[m] overlaps another matrix's S or Z0, or
- * zf_batched_use_graph(0) asks for eager macro-sweeps.  Returns the OR of the warnings, or
+ * most 512, few of them above 320, runs in one kernel instead, each matrix by a team of
+ * workgroups of its own, without lockstep and without the table (the same iterates; only the
+ * rounding of the residual norms differs), unless a Z[m] overlaps another matrix's S or Z0,
+ * or zf_batched_use_graph(0) asks for eager macro-sweeps.  Returns the OR of the warnings, or
  * the first failing matrix's error (every result is still filled).
  */
 int zf_refine_batched(int count, const double* const* S, const double* const* Z0, const int* n,

@@ -871,15 +871,28 @@ static hipError_t macro_sweep(const Launch& L, hipStream_t st) {
 // ---------------------------------------------------------------------------
 // refinement by teams (team.hip)
 // ---------------------------------------------------------------------------
-// A batch whose orders are all at most this is refined by teams, each matrix by its own, with
-// no step that waits for the other matrices.  Teams against macro-sweeps: 8 matrices of N =
-// 64 to 200 256 / 557 us, 48 of 48 to 300 0.81 / 1.57 ms, 160 of 32 to 128 0.57 / 0.94 ms, 128 of
-// 64 to 600 3.9 / 4.2 ms, 16 of 200 to 900 2.52 / 2.56 ms; 512 of 64 to 1024, where 128-wide tiles
-// over the whole chip pay, 31 / 26 ms.
-// ZF_TEAM_BATCH_MAX overrides (0: never; tests and tuning).
-static int team_batch_max() {
+// Whether a batch is refined by teams, each matrix by its own, with no step that waits for the
+// other matrices.  That saves lockstep's launches and waits, 0.3 to 0.5 ms a batch, but a
+// team's 64-wide BF16x3 and 32-wide FP64 tiles have less throughput than lockstep's 128-wide
+// BF16x3 and 64-wide FP64 ones.  A matrix of a full chip takes, by teams / in lockstep, us:
+//   order 192 7.7 / 7.4, 256 12.9 / 13.6, 320 24.6 / 25.6 (lockstep pads it to 384),
+//   384 35.9 / 26.6, 448 54.7 / 48.4 (padded to 512), 512 61 / 50,
+// so what the orders above 320 lose decides.  Batches, by teams / in lockstep, ms: 8 of N = 512
+// 0.68 / 1.3, 32 2.10 / 2.13, 64 4.05 / 3.72, 512 31.2 / 25.8; 32 of N = 384 1.38 / 1.45, 128 4.8 /
+// 3.9, 512 18.4 / 13.6; 64 of N = 448 3.50 / 3.63, 128 7.0 / 6.6; 512 of N = 300 12.5 / 13.1;
+// 48 of N = 48 to 300 0.66 / 1.36, 256 of 64 to 506 4.8 / 5.3, 512 of 64 to 510 9.7 / 9.8, 512 of 256 to
+// 512 20.7 / 18.4.  Above 512 one XCD is too slow for a matrix: 16 of N = 200 to 900 2.52 / 2.56.
+// ZF_TEAM_BATCH_MAX sets the largest order and leaves out the rest (0: never; tests, tuning).
+static bool teams_pay(int count, const int* n) {
+  int max_n = 0;
+  double lost = 0.0;  // us
+  for (int m = 0; m < count; ++m) {
+    max_n = std::max(max_n, n[m]);
+    lost += n[m] > 448 ? 11.0 : n[m] > 384 ? 6.0 : n[m] > 320 ? 9.0 : n[m] > 192 ? -1.0 : 0.0;
+  }
   const char* env = getenv("ZF_TEAM_BATCH_MAX");
-  return env ? std::min(atoi(env), 8192) : 512;
+  if (env) return max_n <= std::min(atoi(env), 8192);
+  return max_n <= 512 && lost <= 500.0;
 }
 
 // Workgroups of the grid: every matrix gets a team in proportion to its 32-wide tiles, such
@@ -1100,7 +1113,7 @@ static int batched_impl(int count, const double* const* S, const double* const* 
   for (int m = 0; m < count; ++m) max_n = std::max(max_n, n[m]);
   // Lockstep reads every S and Z0 before it writes the first Z; a team writes its Z while
   // others have not started, and a matrix redone after a late team reads its inputs last.
-  const bool teams = allow_teams && g_use_graph && max_n <= team_batch_max() &&
+  const bool teams = allow_teams && g_use_graph && teams_pay(count, n) &&
                      !results_overlap_inputs(count, S, Z0, n, Z) && g_b.team_rest.team();
 
   Plan P;

@@ -113,3 +113,15 @@ def test_tile_table_is_for_lockstep(zf, monkeypatch, guess):
     for r in runs.values():
         for a, b in zip(runs["512", 64], r):
             assert torch.equal(a.Z, b.Z) and a.iters == b.iters
+
+
+@pytest.mark.parametrize("orders,teams", [([512] * 8, True), ([384] * 32, True), ([513] + [100] * 8, False),
+                                          ([512] * 48, False), ([384] * 64, False),
+                                          ([300] * 64, True), ([385] * 40 + [200] * 100, True)])
+def test_route_by_work(zf, orders, teams):
+    """Few orders above 320 go by teams, many in lockstep, where the wider tiles pay."""
+    made = {n: _overlap(n, n) for n in set(orders)}
+    out = zf.refine_batched([made[n] for n in orders], refine="off")
+    assert _by_teams(zf) == teams
+    for n, r in zip(orders, out.results):
+        assert torch.equal(r.Z, out.results[orders.index(n)].Z)
