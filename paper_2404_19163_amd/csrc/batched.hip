@@ -895,41 +895,6 @@ static bool teams_pay(int count, const int* n) {
   return max_n <= 512 && lost <= 500.0;
 }
 
-// Workgroups of the grid: every matrix gets a team in proportion to its 32-wide tiles, such
-// that a small batch fills the chip (two workgroups a CU) and a large one queues for it,
-// and goes to the XCD with the least work so far, largest first.  A team's members are
-// consecutive in their XCD's share of the grid, which is dispatched in order, so a team that
-// waits for its last members waits only for teams that are complete.
-static void team_slots(const std::vector<BMat>& mats, std::vector<TeamSlot>& slots) {
-  const int count = (int)mats.size();
-  std::vector<int> order(count);
-  double tiles = 0.0;
-  for (int m = 0; m < count; ++m) {
-    order[m] = m;
-    tiles += (mats[m].np / 32) * (double)(mats[m].np / 32);
-  }
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return mats[a].np > mats[b].np; });
-  // 32-wide tiles a member: what fills 512 places, at most 8 (512 matrices of N = 64 to 256 take
-  // 4.0 ms with 4, 3.7 with 8, 4.6 with 16)
-  const double per = std::min(std::max(tiles / 512.0, 1.0), 8.0);
-  double load[8] = {};
-  std::vector<TeamSlot> run[8];
-  for (int m : order) {
-    const double T = mats[m].np / 32;
-    const int size = std::min(std::max((int)(T * T / per + 0.5), 1), 32);
-    int x = 0;
-    for (int k = 1; k < 8; ++k)
-      if (load[k] < load[x]) x = k;
-    load[x] += T * T * (T + 4.0);
-    for (int r = 0; r < size; ++r) run[x].push_back(TeamSlot{m, (short)r, (short)size});
-  }
-  size_t longest = 0;
-  for (const auto& r : run) longest = std::max(longest, r.size());
-  slots.assign(8 * longest, TeamSlot{-1, 0, 0});
-  for (int x = 0; x < 8; ++x)
-    for (size_t j = 0; j < run[x].size(); ++j) slots[8 * j + x] = run[x][j];
-}
-
 static int grow_pinned(void** p, size_t* cap, size_t need) {
   if (*cap >= need) return 0;
   if (*p) (void)hipHostFree(*p);
@@ -951,8 +916,10 @@ static int run_teams(const std::vector<BMat>& mats, double* partials, const doub
                      const double* const* Z0, double* const* Z, const TeamCall& call, int hcap,
                      hipStream_t st, const TeamOut** outs, const double** hists) {
   const int count = (int)mats.size();
+  std::vector<int> np(count);
+  for (int m = 0; m < count; ++m) np[m] = mats[m].np;
   std::vector<TeamSlot> slots;
-  team_slots(mats, slots);
+  team_slots(np, slots);
   const size_t o_slots = align256(sizeof(TeamMat) * count);
   const size_t up = align256(o_slots + sizeof(TeamSlot) * slots.size());
   const size_t o_hist = align256(up + sizeof(TeamOut) * count);

@@ -1,5 +1,6 @@
-// Host-only check of the batched path's host arithmetic and of the ratio stop rule
-// (zf_index.h) and of the calls after a late team (zf_team.h), built and run by tests/test_host_batch.py under AddressSanitizer and UBSan.  Prints "ok <checks>" or the
+// Host-only check of the batched path's host arithmetic, the ratio stop rule and the blocks'
+// XCDs (zf_index.h), and of the teams' slots and rests (zf_team.h), built and run by
+// tests/test_host_batch.py under AddressSanitizer and UBSan.  Prints "ok <checks>" or the
 // first failure and exits non-zero.
 #include <math.h>
 #include <stdio.h>
@@ -85,6 +86,46 @@ static void powers(std::mt19937& rng) {
               err, prev, pw);
 }
 
+// Every matrix has one team, whole, on one XCD, its members consecutive in that XCD's share of
+// the grid; what is no member's slot is marked so, and no XCD's share ends in a row of them.
+static void slots_of(std::mt19937& rng, int count, int max_np) {
+  std::vector<int> np(count);
+  for (int& v : np) v = 64 * (1 + (int)(rng() % (max_np / 64)));
+  std::vector<TeamSlot> s;
+  team_slots(np, s);
+  CHECK(s.size() % 8 == 0 && !s.empty(), "%zu slots", s.size());
+  std::vector<int> next(count, 0), size(count, 0), at(count, -1);
+  for (int x = 0; x < 8; ++x)
+    for (size_t b = x; b < s.size(); b += 8) {
+      const TeamSlot& t = s[b];
+      if (t.mat < 0) {
+        for (size_t q = b; q < s.size(); q += 8) CHECK(s[q].mat < 0, "a gap in XCD %d's share", x);
+        break;
+      }
+      CHECK(t.mat < count && t.size >= 1 && t.size <= 32 && t.size <= (np[t.mat] / 32) * (np[t.mat] / 32),
+            "matrix %d size %d", t.mat, t.size);
+      CHECK(t.rank == next[t.mat]++ && (at[t.mat] < 0 || at[t.mat] == (int)b - 8),
+            "member %d of matrix %d at %zu", t.rank, t.mat, b);
+      CHECK(t.rank == 0 || size[t.mat] == t.size, "matrix %d changes its size", t.mat);
+      size[t.mat] = t.size;
+      at[t.mat] = (int)b;
+    }
+  for (int m = 0; m < count; ++m) CHECK(next[m] == size[m] && size[m] > 0, "matrix %d has no team", m);
+  size_t last = 0;
+  for (size_t b = s.size() - 8; b < s.size(); ++b) last += s[b].mat >= 0;
+  CHECK(last > 0, "an empty last row");
+}
+
+// Each XCD takes one contiguous run of tiles, in order, also where 8 does not divide the grid:
+// the first nb % 8 XCDs one tile more, the runs one after the other.
+static void runs_of(int nb) {
+  int expect = 0;
+  for (int x = 0; x < 8; ++x)
+    for (int b = x; b < nb; b += 8)
+      CHECK(xcd_remap(b, nb) == expect++, "xcd_remap(%d, %d) = %d", b, nb, xcd_remap(b, nb));
+  CHECK(expect == nb, "%d of %d blocks", expect, nb);
+}
+
 // after a late team the given number of calls go by launches, then a team is tried again
 static void rests() {
   for (int rest : {0, 1, 3, 32}) {
@@ -100,7 +141,10 @@ static void rests() {
 
 int main() {
   rests();
+  for (int nb = 1; nb <= 3000; ++nb) runs_of(nb);
   std::mt19937 rng(7);
+  for (int count : {1, 2, 7, 8, 9, 48, 100, 513, 5000})
+    for (int max_np : {64, 128, 256, 512}) slots_of(rng, count, max_np);
   powers(rng);
   overlaps(rng);
   printf("ok %ld\n", g_checks);

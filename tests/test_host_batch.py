@@ -1,7 +1,7 @@
 """Host-only checks under AddressSanitizer and UBSan: the ratio stop rule (against pow()),
 which batches have results that are other matrices' inputs (against every pair of ranges),
-and how many calls go without a team after a late one.
-Compiled for the host only (hipcc --offload-host-only), so no GPU is needed."""
+the workgroups of teams (whole, consecutive, on one XCD), how many calls go without a team
+after a late one, and the XCDs' runs of tiles for grids that 8 does not divide.  Compiled for the host only (hipcc --offload-host-only), so no GPU is needed."""
 import os
 import shutil
 import subprocess
