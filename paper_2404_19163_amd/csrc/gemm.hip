@@ -307,7 +307,8 @@ hipError_t launch_gemm_x3(const u16* Ahi, const u16* Alo, int lda, const u16* Bh
 // N = 3072 314 / 470 / 807, N = 4096 702 / 902 / 1067.  Only whole rounds of 256-wide tiles,
 // one per CU, are faster: full N = 4096 1189 / 1499 / 1150 us.
 int f32_tile_edge(int M, int N, bool sym) {
-  if (const int want = forced_edge(M, N, sym)) return want;
+  const int want = forced_edge(M, N, sym);
+  if (want == 64 || want == 256) return want;
   const bool whole = M % 256 == 0 && N % 256 == 0 && grid_blocks(M, N, 256, sym) % 256 == 0;
   return whole ? 256 : 64;
 }
@@ -322,8 +323,6 @@ hipError_t launch_gemm_f32(const float* A, int lda, const float* B, int ldb, int
   const int blocks = f32_blocks(M, N, sym);
   if (tile == 256)
     f32_launch<256, 256, 2, 4>(A, lda, B, ldb, M, N, K, sym, blocks, ep, st);
-  else if (tile == 128)
-    f32_launch<128, 128, 2, 2>(A, lda, B, ldb, M, N, K, sym, blocks, ep, st);
   else
     f32_launch<64, 64, 2, 2>(A, lda, B, ldb, M, N, K, sym, blocks, ep, st);
   return hipGetLastError();
