@@ -957,14 +957,16 @@ static int refine_report(int n, bool two, const std::vector<double>& h, const Ph
 }
 
 // Orders that one team refines in one kernel (team.hip).  Past them an XCD's matrix cores
-// bound the products and launches over the whole chip win.  One kernel against launches:
-// mixed N = 64 155 / 281 us, N = 128 177 / 309, N = 256 244 / 345, N = 320 297 / 379, N = 384 374 /
-// 346; FP64 N = 128 148 / 247, N = 192 197 / 274, N = 256 293 / 308, N = 320 431 / 344.
+// bound the products and launches over the whole chip win, the sooner the more of the
+// products are in FP64.  One kernel / launches, us: all FP64 (order 3) N = 128 140 / 180, N = 192
+// 238 / 244, N = 256 297 / 243, N = 320 460 / 278; BF16x3 with FP64 refinement N = 128 158 / 200,
+// N = 192 219 / 255, N = 256 251 / 253, N = 320 303 / 281; without N = 192 154 / 202, N = 256 171 / 202,
+// N = 320 203 / 220, N = 384 321 / 250.
 // ZF_TEAM_MAX overrides (0: never; tests and tuning).
-static int team_max_order(bool fp64) {
+static int team_max_order(bool fp64, bool refine) {
   const char* env = getenv("ZF_TEAM_MAX");
   if (env) return std::min(atoi(env), 2048);
-  return fp64 ? 256 : 320;
+  return fp64 ? 192 : refine ? 256 : 320;
 }
 
 // Longest wait of a team for its members.  A meeting takes 1 us and a solve 0.1 to 0.4 ms, so
@@ -1039,7 +1041,7 @@ static int team_refine(Workspace& w, const double* S, const double* Z0, int n, b
   call.spin = team_spin_ticks(false);
   // A member per 64-wide tile; where FP64 products run too, per 32-wide tile of theirs.  Past
   // 32 members two share a CU, which only the all-FP64 recursion gains from (N = 256: 330 us
-  // with 32 members, 293 with 64; mixed 244 and 266).
+  // with 32 members, 293 with 64; with BF16x3 products 244 and 266).
   const int T = m.np / (fp64 || refine ? 32 : 64);
   w.team->out.done = 0;
   // cleared on the stream of the launch that reads it, as no other stream need be ordered
@@ -1117,7 +1119,7 @@ static int refine_core(const double* S, const double* Z0, int n, const zf_opts& 
   int z0_used = Z0 ? ZF_Z0_GIVEN : ZF_Z0_SCALED_IDENTITY;
   int flags = 0;
   const bool team = (la == AR_X3 || la == AR_F64) && !learned && !log && !g_prof.on &&
-                    (!refine || o.refine == ZF_REFINE_F64_DELTA) && n <= team_max_order(fp64_only) &&
+                    (!refine || o.refine == ZF_REFINE_F64_DELTA) && n <= team_max_order(fp64_only, refine) &&
                     max_l < kTeamHist / 2 && max_h < kTeamHist / 2 - 2;
   if (team && w->team_rest.team()) {
     const int tr = team_refine(*w, S, Z0, n, fp64_only, refine, o, max_l, max_h, Z, st);
