@@ -258,7 +258,8 @@ __device__ __forceinline__ double crt_value(const unsigned (&res)[L], int q4, co
 // column, the FP64 epilogue's unit, whose residues are one word a modulus, and requests
 // the group's L words before using any of them.  Bound by memory (L + 8 to 20 bytes an
 // element) and the FP64 recombination: N = 4096, L = 14, byte loads -> words 145 -> 113 us
-// full, 134 -> 114 us symmetric.
+// full, 134 -> 114 us symmetric.  For 10 moduli or fewer the compiler reserves 48 bytes of
+// scratch memory that no instruction touches (scalar registers kept in vector lanes).
 template <int L>
 __global__ void __launch_bounds__(256)
     crt_reconstruct_kernel(const unsigned char* __restrict__ rho, size_t plane, int np,

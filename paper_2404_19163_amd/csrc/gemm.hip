@@ -154,6 +154,10 @@ static int forced_edge(int M, int N, bool sym) {
 //   symmetric N = 3072 154 / 103 / 111, N = 4096 210 / 170 / 221, N = 5120 314 / 377 / 383.
 // 64 against 128 wide: full N = 1024 14 / 22, N = 1536 33 / 32; symmetric N = 1536 25 / 32,
 // N = 2304 52 / 48.
+// The single-product modes take the same edges: a third of the products on half the operand
+// bytes leaves the edges' order as it is.  (h)(h) solves with every edge forced in turn, N =
+// 500 to 6000: the rule's choice is within 2% of the best one but for full N = 2500 (192 wide
+// 952 us a solve, 128 wide 897).
 int x3_tile_edge(int M, int N, bool sym) {
   const char* env = getenv(sym ? "ZF_X3_SYM_TILE" : "ZF_X3_TILE");
   if (env && atoi(env) == 192 && M >= 192 && N >= 192) return 192;
@@ -256,6 +260,8 @@ template <int PM>
 static void x3_dispatch(const u16* Ahi, const u16* Alo, int lda, const u16* Bhi, const u16* Blo,
                         int ldb, int M, int N, int K, bool sym, int tile, int blocks,
                         const EpiParams& ep, hipStream_t st, int ksa, int ksb) {
+  // 8 waves of 128 x 64.  The three-product kernels fill all 256 registers and keep three values
+  // in scratch memory, stored ahead of the main loop and read back behind it.
   if (tile == 256)
     x3_launch<256, 256, 2, 4, PM, 2, 1>(Ahi, Alo, lda, Bhi, Blo, ldb, M, N, K, sym, blocks, ep, st,
                                         ksa, ksb);
@@ -300,7 +306,7 @@ hipError_t launch_gemm_x3(const u16* Ahi, const u16* Alo, int lda, const u16* Bh
   return hipGetLastError();
 }
 
-// FP32 tile edge.  Its matrix-core instruction takes twice as long for the same fragments as
+// FP32 tile edge: 64 or 256.  Its matrix-core instruction takes twice as long for the same fragments as
 // a BF16 one, so a 64-wide tile is not held back by operand traffic and, four blocks a CU,
 // leaves the least of the chip idle: 64 / 128 / 256 wide full N = 1024 40 / 89 / 275 us,
 // N = 2048 167 / 175 / 543, N = 3072 527 / 614 / 833, N = 5120 2330 / 2804 / 2780; symmetric

@@ -1,19 +1,19 @@
 // A whole refinement in one kernel: for orders where a product takes less than the launch
 // that carries it.
 //
-// A team of up to 32 workgroups runs set-up, both phases and the copy-out of one matrix,
-// meeting between stages instead of ending a kernel.  Its members run on one XCD, whose L2
-// they share, so a meeting needs no cache maintenance: every wave waits for its stores to
-// reach L2, one thread per workgroup counts itself in, and later loads of data that the
+// A team of up to 64 workgroups (more than 32 only where every product is in FP64) runs
+// set-up, both phases and the copy-out of one matrix, meeting between stages instead of
+// ending a kernel.  Its members run on one XCD, whose L2 they share, so a meeting needs no
+// cache maintenance: every wave waits for its stores to reach L2, one thread per workgroup counts itself in, and later loads of data that the
 // kernel has written go past the CU's own cache (sc1).  Measured on gfx950: 1.0-1.2 us per
 // meeting of 16-32 workgroups, against 1.9-3.0 us with agent-scope fences over all XCDs, and
 // 4-5 us for the end of a kernel and the start of the next.  Workgroup b of a grid is
 // dispatched to XCD b % 8; the members compare XCD numbers when they first meet, and if
 // they differ the team uses agent-scope fences throughout, so only speed depends on it.
 //
-// The recursion, the stop test and the arithmetic are those of zf_refine_ex; every member
-// evaluates the stop test from the same partial sums in the same order, so the team agrees
-// without another meeting.
+// The recursion, the stop test (above_power) and the arithmetic are those of separate
+// launches; every member evaluates the stop test from the same partial sums in the same
+// order, so the team agrees without another meeting.
 //
 // A wait is bounded (TeamCall::spin): a member that runs out of time poisons the counter,
 // every member leaves, nothing has been written to Z, and the host runs the matrix by
