@@ -377,6 +377,18 @@ hipError_t launch_norm_finalize(const double* partials, int count, double* out, 
   return hipGetLastError();
 }
 
+// M's strict lower triangle from its upper (np x np).
+__global__ void mirror_upper_kernel(double* M, int np) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
+  if (j < i) M[(size_t)i * np + j] = M[(size_t)j * np + i];
+}
+
+hipError_t launch_mirror_upper(double* M, int np, hipStream_t st) {
+  if (np % 64 != 0 || np > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(mirror_upper_kernel, dim3((np + 255) / 256, np), dim3(256), 0, st, M, np);
+  return hipGetLastError();
+}
+
 __global__ void fill_zero_kernel(uint32_t* p, size_t words) {
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < words;
        e += (size_t)gridDim.x * blockDim.x)

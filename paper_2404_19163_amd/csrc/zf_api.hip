@@ -1598,6 +1598,8 @@ static int t_gemm_impl(int precision, int oz_slices, int sym, int m, int nn, int
   pad_in(A, m, k, a64);
   pad_in(B, nn, k, b64);
   if (D) pad_in(D, m, nn, d64);
+  // symmetric mode takes C from the triangle above the diagonal, D's part included
+  if (D && sym && he == hipSuccess) he = launch_mirror_upper(d64, np, st);
   if (he == hipSuccess) he = hipMemsetAsync(c64, 0, e * 8, st);
   EpiParams ep = epi0(np, m < nn ? m : nn);
   ep.kb = 0;  // this entry's operands and outputs are row-major
